@@ -78,8 +78,8 @@ struct Cfg {
   static_assert(A_DMA * RPD * WAVES == BM && B_DMA * RPD_B * WAVES == BN, "DMA split");
   static_assert(!W8 || BK == 64, "fp8 weight rows are 64 bytes");
 };
-using CfgLarge = Cfg<256, 256, 4, 2, 2, 64>;  // prefill: 8 waves of 64 x 128, 2 x 64 KiB stages
-// decode-shaped: 4 waves, 3 x 24 KiB stages, streamed weights
+// decode-shaped: 4 waves, 3 x 24 KiB stages, streamed weights (bf16 batches of at least 128
+// rows per expert run on the 256 x 256 kernel of gemm256.hip)
 using CfgSmall = Cfg<64, 128, 1, 4, 3, 64, 2, true, true>;
 // fp8 weights: the smaller weight tiles leave room for a third stage (3 x 48 KiB) in the
 // prefill configuration. The decode one takes 256 weight rows per tile, so that a K step
@@ -91,17 +91,6 @@ using CfgLarge8 = Cfg<256, 256, 4, 2, 3, 64, 1, true, false, true>;
 using CfgSmall8 = Cfg<64, 256, 1, 4, 3, 64, 2, true, false, true>;
 
 constexpr int MAXG = 2 * PMPE_MAX_POOL + 1;  // routed experts + the shared group
-
-// DMA of 4 bytes per lane (int32 gather indices): lane l's word lands at lds_base + 4 * l.
-__device__ __forceinline__ void dma4(const void* src, uint32_t lds_base_) {
-  const uint32_t lds_base = __builtin_amdgcn_readfirstlane(lds_base_);
-  asm volatile(
-      "s_mov_b32 m0, %1\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dword %0, off" ::"v"(src),
-      "s"(lds_base)
-      : "memory", "m0");
-}
 
 // Rows of the output tile staged per epilogue pass: the largest multiple of 16 that
 // divides BM and whose bf16 rows fit in one ring stage.
@@ -512,7 +501,7 @@ __global__ __launch_bounds__(C::THREADS) void gemm_bf16_kernel(FfnArgs a) {
             for (int i = 0; i < 4; ++i) {
               const int r = r0 - pass * ER + (lane >> 4) * 4 + i;
               const int c = wn * WCOLS + nb * 16 + (lane & 15);
-              const float v = GATED ? silu(acc[mb][nb][i] * sg) * (acc[mb][nb + NBO][i] * su)
+              const float v = GATED ? silu_to_bf16(acc[mb][nb][i] * sg) * (acc[mb][nb + NBO][i] * su)
                                     : acc[mb][nb][i] * sg;
               so[r * NCOLS + c] = (uint16_t)f32_to_bf16_rne(v);
               if constexpr (GATED && SAVE) {
@@ -907,10 +896,8 @@ hipError_t launch_grouped_nt_gemm(const FfnArgs& a, hipStream_t s) {
     else
       hipLaunchKernelGGL((gemm_bf16_kernel<C, false, false, false>), dim3((unsigned)g), dim3(C::THREADS), 0, s, a);
   };
-  if (large)
-    run(CfgLarge{});
-  else
-    run(CfgSmall{});
+  if (large) return launch_gemm256_plain(a, s);
+  run(CfgSmall{});
   return hipGetLastError();
 }
 
@@ -918,7 +905,7 @@ hipError_t launch_grouped_nt_gemm(const FfnArgs& a, hipStream_t s) {
 hipError_t launch_expert_ffn_parts(const FfnArgs& a, hipStream_t s, int parts) {
   const int E = a.n_pub + a.n_priv;
   if (a.act_bf16) {
-    // Average rows per routed expert picks the tile shape.
+    // Average rows per routed expert picks the tile shape: from 128 on the 256 x 256 kernel.
     const bool large = (int64_t)a.T * a.k >= (int64_t)128 * E;
     int dev = 0, ncu = 256;
     if (hipGetDevice(&dev) == hipSuccess) {
@@ -939,13 +926,9 @@ hipError_t launch_expert_ffn_parts(const FfnArgs& a, hipStream_t s, int parts) {
       return dim3((unsigned)g);
     };
     if (large) {
-      using C = CfgLarge;
-      if ((parts & 1) && a.ab_save)
-        hipLaunchKernelGGL((gemm_bf16_kernel<C, true, true>), grid(C::BM, C::BN / 2, true, C::PER_CU), dim3(C::THREADS), 0, s, a);
-      else if (parts & 1)
-        hipLaunchKernelGGL((gemm_bf16_kernel<C, true>), grid(C::BM, C::BN / 2, true, C::PER_CU), dim3(C::THREADS), 0, s, a);
-      if (parts & 2)
-        hipLaunchKernelGGL((gemm_bf16_kernel<C, false>), grid(C::BM, C::BN, false, C::PER_CU), dim3(C::THREADS), 0, s, a);
+      hipError_t e = (parts & 1) ? launch_gemm256_up(a, s) : hipSuccess;
+      if (e == hipSuccess && (parts & 2)) e = launch_gemm256_down(a, s);
+      return e;
     } else {
       using C = CfgSmall;
       if ((parts & 1) && a.ab_save)

@@ -55,6 +55,17 @@ __device__ __forceinline__ void dma16s(uint32_t byte_off, const void* base_, uin
         : "memory", "m0");
 }
 
+// DMA of 4 bytes per lane (int32 gather indices): lane l's word lands at lds_base + 4 * l.
+__device__ __forceinline__ void dma4(const void* src, uint32_t lds_base_) {
+  const uint32_t lds_base = __builtin_amdgcn_readfirstlane(lds_base_);
+  asm volatile(
+      "s_mov_b32 m0, %1\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dword %0, off" ::"v"(src),
+      "s"(lds_base)
+      : "memory", "m0");
+}
+
 // f(integral_constant<I>), ..., f(integral_constant<N-1>): copies whose LDS offset is an
 // immediate (IMM of dma16s) are issued from a compile-time index.
 template <int I, int N>

@@ -37,6 +37,10 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
 }
 
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + __expf(-g)); }
+// The same with the hardware reciprocal (1 ulp) in place of the correctly rounded division (ten
+// more operations), for results that are rounded to bf16; every bf16 path uses this one, so
+// that their h agree to the bit.
+__device__ __forceinline__ float silu_to_bf16(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
 
 // SwiGLU backward of one element: upstream d = dL/dh, gate projection g, up projection u;
 // h = silu(g) u, da = d u s (1 + g (1 - s)), db = d g s with s = sigmoid(g).
@@ -161,6 +165,10 @@ hipError_t launch_expert_ffn(const FfnArgs& a, hipStream_t s);
 hipError_t launch_expert_ffn_parts(const FfnArgs& a, hipStream_t s, int parts);
 hipError_t launch_grouped_nt_gemm(const FfnArgs& a, hipStream_t s);
 hipError_t launch_expert_ffn_fp8(const FfnArgs& a, hipStream_t s);
+// bf16 grouped GEMM on 256 x 256 tiles: GEMM1 + SwiGLU, GEMM2 + audit, plain product
+hipError_t launch_gemm256_up(const FfnArgs& a, hipStream_t s);
+hipError_t launch_gemm256_down(const FfnArgs& a, hipStream_t s);
+hipError_t launch_gemm256_plain(const FfnArgs& a, hipStream_t s);
 
 struct LoraArgs {
   int T, H, I, k, n_pub, n_priv, rank, gate;
