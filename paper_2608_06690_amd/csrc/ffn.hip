@@ -78,8 +78,8 @@ struct Cfg {
   static_assert(A_DMA * RPD * WAVES == BM && B_DMA * RPD_B * WAVES == BN, "DMA split");
   static_assert(!W8 || BK == 64, "fp8 weight rows are 64 bytes");
 };
-// decode-shaped: 4 waves, 3 x 24 KiB stages, streamed weights (bf16 batches of at least 128
-// rows per expert run on the 256 x 256 kernel of gemm256.hip)
+// decode-shaped: 4 waves, 3 x 24 KiB stages, streamed weights (larger bf16 batches run on the
+// 256 x 256 kernel of gemm256.hip, see use_gemm256)
 using CfgSmall = Cfg<64, 128, 1, 4, 3, 64, 2, true, true>;
 // fp8 weights: the smaller weight tiles leave room for a third stage (3 x 48 KiB) in the
 // prefill configuration. The decode one takes 256 weight rows per tile, so that a K step
@@ -907,6 +907,23 @@ void launch_f32(const FfnArgs& a, hipStream_t s, int parts) {
 
 }  // namespace
 
+namespace {
+// Which bf16 grouped products (N = a.H output columns of the last one) run on the 256 x 256
+// kernel: by the average rows per routed expert, as the host does not know the counts. Its
+// tiles read a weight once per 256 rows where the 64-row tiles read it once per 64, so they win
+// as soon as many experts exceed 64 rows (Qwen3-30B-A3B-shaped expert FFN, us with 64-row /
+// 256-row tiles: 512 tokens 313 / 320, 768 331 / 331, 1536 421 / 377, 2048 563 / 409, 2500 639
+// / 402; all in the public pool 512 215 / 250, 1111 400 / 285; DeepSeek-V2-Lite-shaped 400
+// 305 / 312, 800 462 / 370, 1600 744 / 445): from 48 rows on. With fewer than two such tiles
+// per CU the larger tiles leave CUs idle and the line lies at 112 rows (52 experts of 1664 x
+// 640: 1111 tokens, 85 rows, 105 / 136; 1536 tokens, 118 rows, 158 / 137).
+bool use_gemm256(const FfnArgs& a) {
+  const int64_t rows = (int64_t)a.T * a.k, E = a.n_pub + a.n_priv;
+  const bool few_tiles = E * ((a.H + 255) / 256) < 512;
+  return rows >= (few_tiles ? 112 : 48) * E;
+}
+}  // namespace
+
 hipError_t launch_expert_ffn(const FfnArgs& a, hipStream_t s) { return launch_expert_ffn_parts(a, s, 3); }
 
 // fp8 expert weights (routed experts only, no shared group): the same two GEMMs.
@@ -917,7 +934,10 @@ hipError_t launch_expert_ffn_fp8(const FfnArgs& a, hipStream_t s) {
     int v = 0;
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) ncu = v;
   }
-  const bool large = (int64_t)a.T * a.k >= (int64_t)128 * E;
+  // The 64-row tiles with two blocks per CU win up to several hundred rows per expert
+  // (Qwen3-30B-A3B-shaped layer pass, us with 64-row / 256-row tiles: 1111 tokens 282 / 362,
+  // 2600 395 / 445, 4096 545 / 554, 8192 954 / 968, 16384 1,749 / 1,666).
+  const bool large = (int64_t)a.T * a.k >= (int64_t)768 * E;
   auto run = [&](auto cfg) {
     using C = decltype(cfg);
     auto grid = [&](int ncols, bool gemm1) {
@@ -955,7 +975,7 @@ hipError_t launch_grouped_nt_gemm(const FfnArgs& a, hipStream_t s) {
     int v = 0;
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) ncu = v;
   }
-  const bool large = (int64_t)a.T * a.k >= (int64_t)128 * E;
+  if (use_gemm256(a)) return launch_gemm256_plain(a, s);
   auto run = [&](auto cfg) {
     using C = decltype(cfg);
     int64_t tiles = ((int64_t)a.T * a.k / C::BM + E) * ((a.H + C::BN - 1) / C::BN);
@@ -966,7 +986,6 @@ hipError_t launch_grouped_nt_gemm(const FfnArgs& a, hipStream_t s) {
     else
       hipLaunchKernelGGL((gemm_bf16_kernel<C, false, false, false>), dim3((unsigned)g), dim3(C::THREADS), 0, s, a);
   };
-  if (large) return launch_gemm256_plain(a, s);
   run(CfgSmall{});
   return hipGetLastError();
 }
@@ -975,8 +994,6 @@ hipError_t launch_grouped_nt_gemm(const FfnArgs& a, hipStream_t s) {
 hipError_t launch_expert_ffn_parts(const FfnArgs& a, hipStream_t s, int parts) {
   const int E = a.n_pub + a.n_priv;
   if (a.act_bf16) {
-    // Average rows per routed expert picks the tile shape: from 128 on the 256 x 256 kernel.
-    const bool large = (int64_t)a.T * a.k >= (int64_t)128 * E;
     int dev = 0, ncu = 256;
     if (hipGetDevice(&dev) == hipSuccess) {
       int v = 0;
@@ -995,7 +1012,7 @@ hipError_t launch_expert_ffn_parts(const FfnArgs& a, hipStream_t s, int parts) {
       if (tiles < g) g = (tiles + 7) / 8 * 8;
       return dim3((unsigned)g);
     };
-    if (large) {
+    if (use_gemm256(a)) {
       hipError_t e = (parts & 1) ? launch_gemm256_up(a, s) : hipSuccess;
       if (e == hipSuccess && (parts & 2)) e = launch_gemm256_down(a, s);
       return e;

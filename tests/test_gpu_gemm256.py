@@ -1,4 +1,4 @@
-"""The 256 x 256 grouped GEMM (batches of at least 128 rows per expert on average) at the edges
+"""The 256 x 256 grouped GEMM (batches of many rows per expert on average) at the edges
 of its tiles: row counts around 128 and 256, K loops of one to a few steps, output widths that
 are not multiples of a tile, gathered and permuted rows, the shared group, saved projections."""
 import numpy as np
@@ -84,3 +84,27 @@ def test_tile_edges(counts, hidden, inter, form):
     assert torch.equal(audit, want)
     assert calls.tolist() == [int(c > 0) for c in counts[n:]]
     assert int(status) == 0
+
+
+@pytest.mark.parametrize("tokens", [48 * 64 - 1, 48 * 64])  # last batch of the 64-row tiles, first of the 256-row ones
+def test_both_sides_of_the_tile_choice(tokens):
+    n, hidden, inter = 32, 2048, 64
+    d = P.make_desc(hidden, inter, n, n, 1)
+    g = torch.Generator(device="cuda").manual_seed(tokens)
+    x = torch.empty(tokens, hidden, dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    w13 = torch.empty(2 * n, 2 * inter, hidden, dtype=torch.bfloat16, device="cuda").normal_(0, hidden ** -0.5, generator=g)
+    w2 = torch.empty(2 * n, hidden, inter, dtype=torch.bfloat16, device="cuda").normal_(0, inter ** -0.5, generator=g)
+    expert = torch.sort(torch.randint(0, 2 * n, (tokens,), generator=g, device="cuda")).values
+    count = torch.bincount(expert, minlength=2 * n).to(torch.int32)
+    offset = torch.cat([torch.zeros(1, dtype=torch.int64, device="cuda"), count.cumsum(0)]).to(torch.int32)
+    row_token = torch.randperm(tokens, generator=g, device="cuda").to(torch.int32)
+    y = torch.empty(tokens, hidden, dtype=torch.bfloat16, device="cuda")
+    audit = torch.zeros(tokens, dtype=torch.int32, device="cuda")
+    ws = torch.empty(P.pmpe_workspace_bytes(d, tokens), dtype=torch.uint8, device="cuda")
+    P.pmpe_expert_ffn(d, tokens, None, x, count, offset, row_token, w13[:n], w2[:n], w13[n:], w2[n:], None, None, None,
+                      y, audit, None, None, ws)
+    for e in range(2 * n):
+        sl = slice(int(offset[e]), int(offset[e + 1]))
+        _, y_ref = reference(x, row_token[sl].long(), w13[e], w2[e], inter)
+        assert C.rel_l2(y[sl].cpu().double().numpy(), y_ref.cpu().double().numpy()) <= C.RTOL_ROW_BF16, e
+    assert int(audit.sum()) == int(count[n:].sum())
