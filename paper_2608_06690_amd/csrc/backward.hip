@@ -405,63 +405,73 @@ __global__ __launch_bounds__(BT) void bwd_swiglu_kernel(BwdArgs a, const float* 
   }
 }
 
-// Softmax over the whole permitted pool (POOL_SOFTMAX), block t: the pool logits
-// z_e = x_t . W_r[e] (+ b_e) are recomputed in fp32 (one wave per logit, fixed-order
-// reduction), p = softmax(z), and dz_e = p_e ([e selected] dg_e - sum_sel p_i dg_i) for
-// every pool member e, written to dz_pool[t, e - first id of the pool].
-__global__ __launch_bounds__(BT) void bwd_pool_dz_kernel(BwdArgs a) {
-  extern __shared__ float s_dyn[];
-  float* s_x = s_dyn;               // [H]
-  float* s_z = s_dyn + a.H;         // [pool]
-  __shared__ float s_red[2];
-  const int t = blockIdx.x, H = a.H, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// Softmax over the whole permitted pool (POOL_SOFTMAX), one wave per token: from the pool
+// logits z_e = x_t . W_r[e] (+ b_e), recomputed by the forward's router kernel (its partial sums
+// over H added in order), p = softmax(z) and dz_e = p_e ([e selected] dg_e - sum_sel p_i dg_i)
+// for every pool member e, written to dz_pool[t, e - first id of the pool] (z may be dz_pool).
+// A logit per wave with x staged in LDS, as before, read 4 H bytes of router rows per logit:
+// 184 us for 2000 tokens of H 2048 over pools of 64 and 16; the router kernel and this one 28.
+__global__ __launch_bounds__(BT) void bwd_pool_dz_kernel(BwdArgs a, const float* z, int zsplit) {
+  constexpr int NPL = 2 * PMPE_MAX_POOL / 64;  // pool members per lane
+  const int t = blockIdx.x * (BT / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (t >= a.T) return;  // wave-uniform; no block barrier follows
   // the pool of the token is the one its selection lies in (a masked route never mixes
   // pools; the soft control ranks the concatenated pool)
-  const bool priv = a.topk_idx[t * a.k] >= a.n_pub;
+  const bool priv = a.topk_idx[(size_t)t * a.k] >= a.n_pub;
   const int first = a.soft ? 0 : (priv ? a.n_pub : 0);
   const int pool = a.soft ? a.n_pub + a.n_priv : (priv ? a.n_priv : a.n_pub);
-  const uint16_t* xt = (const uint16_t*)a.x + (size_t)t * H;
-  for (int h = tid; h < H; h += BT) s_x[h] = bf16_to_f32(xt[h]);
-  __syncthreads();
-  for (int i = wave; i < pool; i += BT / 64) {
-    const int e = first + i;
-    const float* w = e < a.n_pub ? a.wr_pub + (size_t)e * H : a.wr_priv + (size_t)(e - a.n_pub) * H;
-    float s = 0.f;
-    for (int h = lane; h < H; h += 64) s += s_x[h] * w[h];
-    s = wave_sum(s);
-    if (lane == 0) s_z[i] = a.bias ? s + a.bias[e] : s;
+  // slot j = lane: the selected expert's position in the pool and its gate gradient
+  int sel = -1;
+  float dg = 0.f;
+  if (lane < a.k) {
+    sel = a.topk_idx[(size_t)t * a.k + lane] - first;
+    dg = a.dz_row[a.token_row[(size_t)t * a.k + lane]];
   }
-  __syncthreads();
-  if (tid == 0) {
-    float mx = -INFINITY;
-    for (int i = 0; i < pool; ++i) mx = fmaxf(mx, s_z[i]);
-    float den = 0.f;
-    for (int i = 0; i < pool; ++i) den += __expf(s_z[i] - mx);
-    // sum over the selection of p_i dg_i (dg per slot from the row pass)
-    float sel = 0.f;
-    for (int j = 0; j < a.k; ++j) {
-      const int e = a.topk_idx[t * a.k + j];
-      sel += __expf(s_z[e - first] - mx) / den * a.dz_row[a.token_row[t * a.k + j]];
+  const float* zt = z + (size_t)t * a.pool_stride;
+  const size_t pstride = (size_t)a.T * a.pool_stride;
+  float v[NPL], u[NPL], mx = -INFINITY;
+#pragma unroll
+  for (int r = 0; r < NPL; ++r) {
+    const int i = r * 64 + lane;
+    v[r] = -INFINITY;
+    u[r] = 0.f;
+    if (i < pool) {
+      v[r] = zt[i];
+      for (int p = 1; p < zsplit; ++p) v[r] += zt[p * pstride + i];
     }
-    s_red[0] = mx;
-    s_red[1] = den;
-    s_z[pool] = sel;  // scratch slot after the pool
+    mx = fmaxf(mx, v[r]);
   }
-  __syncthreads();
-  const float mx = s_red[0], den = s_red[1], sel = s_z[pool];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+  for (int j = 0; j < a.k; ++j) {
+    const int sj = __shfl(sel, j, 64);
+    const float dj = __shfl(dg, j, 64);
+#pragma unroll
+    for (int r = 0; r < NPL; ++r)
+      if (r * 64 + lane == sj) u[r] = dj;
+  }
+  float den = 0.f, sum = 0.f;
+#pragma unroll
+  for (int r = 0; r < NPL; ++r) {
+    v[r] = (r * 64 + lane < pool) ? __expf(v[r] - mx) : 0.f;
+    den += v[r];
+  }
+  den = wave_sum(den);
+#pragma unroll
+  for (int r = 0; r < NPL; ++r) {
+    v[r] = v[r] / den;
+    sum += v[r] * u[r];
+  }
+  sum = wave_sum(sum);
   float* dzp = a.dz_pool + (size_t)t * a.pool_stride;
-  for (int i = tid; i < pool; i += BT) {
-    const float pe = __expf(s_z[i] - mx) / den;
-    float u = 0.f;
-    for (int j = 0; j < a.k; ++j)
-      if (a.topk_idx[t * a.k + j] == first + i) u = a.dz_row[a.token_row[t * a.k + j]];
-    dzp[i] = pe * (u - sel);
-  }
+#pragma unroll
+  for (int r = 0; r < NPL; ++r)
+    if (r * 64 + lane < pool) dzp[r * 64 + lane] = v[r] * (u[r] - sum);
 }
 
 // dx_t = sum_j dXr[r_j] (slot order) + router term + shared-expert term, eight columns per
-// thread (the k rows' loads are all issued before the ordered sum). Router term: RENORM
-// sum_j dz_j W_r[e_j]; POOL_SOFTMAX sum over the pool of dz_e W_r[e] in id order.
+// thread (the k rows' loads are all issued before the ordered sum). Router term (RENORM):
+// sum_j dz_j W_r[e_j].
 template <bool NT>  // NT: bf16 row input gradients (the NT path), else fp32
 __global__ __launch_bounds__(BT) void bwd_dx_kernel(BwdArgs a) {
   __shared__ int s_r[PMPE_MAX_TOPK];
@@ -472,13 +482,9 @@ __global__ __launch_bounds__(BT) void bwd_dx_kernel(BwdArgs a) {
     const int r = a.token_row[t * k + tid];
     s_r[tid] = r;
     s_e[tid] = a.topk_idx[t * k + tid];
-    s_dz[tid] = a.pool_gates ? 0.f : a.dz_row[r];
+    s_dz[tid] = a.dz_row[r];
   }
   __syncthreads();
-  const bool priv = a.topk_idx[t * k] >= a.n_pub;
-  const int first = a.soft ? 0 : (priv ? a.n_pub : 0);
-  const int pool = a.soft ? a.n_pub + a.n_priv : (priv ? a.n_priv : a.n_pub);
-  const float* dzp = a.pool_gates ? a.dz_pool + (size_t)t * a.pool_stride : nullptr;
   for (int h = tid * 8; h < H; h += BT * 8) {
     f32x4 s[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
     // up to eight rows in flight, summed in slot order. The slots' rows, experts and dz are
@@ -522,12 +528,6 @@ __global__ __launch_bounds__(BT) void bwd_dx_kernel(BwdArgs a) {
         }
       }
     }
-    for (int i = 0; dzp && i < pool; ++i) {
-      const int e = first + i;
-      const float* w = e < a.n_pub ? a.wr_pub + (size_t)e * H : a.wr_priv + (size_t)(e - a.n_pub) * H;
-#pragma unroll
-      for (int q = 0; q < 2; ++q) s[q] += dzp[i] * *(const f32x4*)(w + h + 4 * q);
-    }
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       if (a.dXsh) s[q] += *(const f32x4*)(a.dXsh + (size_t)t * H + h + 4 * q);
@@ -536,31 +536,158 @@ __global__ __launch_bounds__(BT) void bwd_dx_kernel(BwdArgs a) {
   }
 }
 
-// POOL_SOFTMAX router-row gradient of private expert p: every token whose pool holds p
-// contributes dz x_t (the gradient is dense over the pool). Block (p, c) sums a fixed
-// chunk of tokens in ascending order, eight columns per thread.
-__global__ __launch_bounds__(BT) void bwd_dwr_pool_part_kernel(BwdArgs a) {
-  const int pe = blockIdx.x, c = blockIdx.y, H = a.H, T = a.T;
-  if (c == 0 && threadIdx.x == 0 && a.grad_rows) a.grad_rows[pe] = (uint32_t)a.count[a.n_pub + pe];
-  const int per = (T + BWD_DWR_SPLIT - 1) / BWD_DWR_SPLIT;
-  const int t0 = min(T, c * per), t1 = min(T, (c + 1) * per);
-  float* part = a.dwr_part + ((size_t)pe * BWD_DWR_SPLIT + c) * H;
-  const uint16_t* x = (const uint16_t*)a.x;
-  for (int h = threadIdx.x * 8; h < H; h += BT * 8) {
-    float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int t = t0; t < t1; ++t) {
-      if (!a.soft && a.topk_idx[t * a.k] < a.n_pub) continue;  // a public-pool token
-      const int idx = a.soft ? a.n_pub + pe : pe;
-      const float dz = a.dz_pool[(size_t)t * a.pool_stride + idx];
-      const u32x4 v = *(const u32x4*)(x + (size_t)t * H + h);
+// The same with POOL_SOFTMAX gates, whose router term is dense: sum over the token's pool of
+// dz_e W_r[e] in id order. A block takes four tokens, so that the pool's router rows are read
+// once for four (51 -> 32 us for 2000 tokens of H 2048 over pools of 64 and 16).
+constexpr int DXP_T = 4;
+template <bool NT>
+__global__ __launch_bounds__(BT) void bwd_dx_pool_kernel(BwdArgs a) {
+  __shared__ int s_r[DXP_T][PMPE_MAX_TOPK];
+  __shared__ __attribute__((aligned(16))) float s_dz[2 * PMPE_MAX_POOL][DXP_T];
+  const int t0 = blockIdx.x * DXP_T, H = a.H, k = a.k, tid = threadIdx.x;
+  const int nt = min(DXP_T, a.T - t0);
+  if (tid < DXP_T * PMPE_MAX_TOPK) {
+    const int tt = tid / PMPE_MAX_TOPK, j = tid % PMPE_MAX_TOPK;
+    if (tt < nt && j < k) s_r[tt][j] = a.token_row[(size_t)(t0 + tt) * k + j];
+  }
+  // pool of each token: bit tt of privs (block-uniform)
+  int privs = 0;
+  for (int tt = 0; tt < nt; ++tt) privs |= (a.topk_idx[(size_t)(t0 + tt) * k] >= a.n_pub ? 1 : 0) << tt;
+  const int all = (1 << nt) - 1;
+  for (int i = tid; i < nt * a.pool_stride; i += BT)  // (entries past a token's pool are not used)
+    s_dz[i % a.pool_stride][i / a.pool_stride] = a.dz_pool[(size_t)t0 * a.pool_stride + i];
+  __syncthreads();
+  for (int h = tid * 8; h < H; h += BT * 8) {
+    f32x4 s[DXP_T][2];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        s[2 * q] += dz * bf16_to_f32(v[q] & 0xFFFFu);
-        s[2 * q + 1] += dz * bf16_to_f32(v[q] >> 16);
+    for (int tt = 0; tt < DXP_T; ++tt) {
+      s[tt][0] = s[tt][1] = f32x4{0, 0, 0, 0};
+      if (tt >= nt) continue;
+      for (int j0 = 0; j0 < k; j0 += 8) {
+        // eight rows in flight, unconditional (slots past k reload slot k - 1), summed in order
+        f32x4 d[8][2];
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) {
+          const size_t r = (size_t)s_r[tt][min(j0 + jj, k - 1)];
+          if constexpr (NT) {
+            const u32x4 v = __builtin_nontemporal_load((const u32x4*)((const uint16_t*)a.dXr + r * H + h));
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+              d[jj][q] = f32x4{bf16_to_f32(v[2 * q] & 0xFFFFu), bf16_to_f32(v[2 * q] >> 16),
+                               bf16_to_f32(v[2 * q + 1] & 0xFFFFu), bf16_to_f32(v[2 * q + 1] >> 16)};
+          } else {
+            d[jj][0] = *(const f32x4*)(a.dXr + r * H + h);
+            d[jj][1] = *(const f32x4*)(a.dXr + r * H + h + 4);
+          }
+        }
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj)
+          if (j0 + jj < k) {
+            s[tt][0] += d[jj][0];
+            s[tt][1] += d[jj][1];
+          }
       }
     }
-    *(f32x4*)(part + h) = f32x4{s[0], s[1], s[2], s[3]};
-    *(f32x4*)(part + h + 4) = f32x4{s[4], s[5], s[6], s[7]};
+    // n router rows of w for the tokens in `who`, from position pos of their dz rows on
+    auto rows = [&](const float* w, int n, int pos, int who) {
+      // eight rows' loads in flight (rows past n reload row n - 1 and are not added)
+      for (int i0 = 0; i0 < n; i0 += 8) {
+        f32x4 w0[8], w1[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float* p = w + (size_t)min(i0 + i, n - 1) * H + h;
+          w0[i] = *(const f32x4*)p;
+          w1[i] = *(const f32x4*)(p + 4);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          if (i0 + i >= n) continue;
+          const f32x4 dz = *(const f32x4*)&s_dz[pos + i0 + i][0];
+#pragma unroll
+          for (int tt = 0; tt < DXP_T; ++tt) {
+            if (who & (1 << tt)) {
+              s[tt][0] += dz[tt] * w0[i];
+              s[tt][1] += dz[tt] * w1[i];
+            }
+          }
+        }
+      }
+    };
+    const int pub = a.soft ? all : (all & ~privs), prv = a.soft ? all : privs;
+    if (pub) rows(a.wr_pub, a.n_pub, 0, pub);
+    if (prv) rows(a.wr_priv, a.n_priv, a.soft ? a.n_pub : 0, prv);
+#pragma unroll
+    for (int tt = 0; tt < DXP_T; ++tt) {
+      if (tt >= nt) continue;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const size_t o = (size_t)(t0 + tt) * H + h + 4 * q;
+        if (a.dXsh) s[tt][q] += *(const f32x4*)(a.dXsh + o);
+        *(f32x4*)(a.dx + o) = s[tt][q];
+      }
+    }
+  }
+}
+
+// POOL_SOFTMAX router-row gradients: every token whose pool holds the private experts
+// contributes dz x_t to each of them (the gradient is dense over the pool). Block (x, c, z)
+// sums chunk c of the tokens in ascending order for DWP_E experts at once, two columns per
+// thread, so that a token's x is read once for all of them (83 -> 35 us for 2000 tokens of H
+// 2048 and 16 private experts; a block per expert read x 16 times with one token in flight).
+constexpr int DWP_E = 16, DWP_THREADS = 128, DWP_H = DWP_THREADS * 2, DWP_B = 64;
+__global__ __launch_bounds__(DWP_THREADS) void bwd_dwr_pool_part_kernel(BwdArgs a) {
+  __shared__ __attribute__((aligned(16))) float s_dz[DWP_B][DWP_E];  // a batch of tokens
+  __shared__ int s_mine[DWP_B];  // the token's pool holds the private experts
+  const int c = blockIdx.y, pe0 = blockIdx.z * DWP_E, H = a.H, T = a.T, tid = threadIdx.x;
+  const int ne = min(DWP_E, a.n_priv - pe0);
+  if (blockIdx.x == 0 && c == 0 && tid < ne && a.grad_rows)
+    a.grad_rows[pe0 + tid] = (uint32_t)a.count[a.n_pub + pe0 + tid];
+  const int per = (T + BWD_DWR_SPLIT - 1) / BWD_DWR_SPLIT;
+  const int t0 = min(T, c * per), t1 = min(T, (c + 1) * per);
+  const int h = blockIdx.x * DWP_H + tid * 2;
+  const bool in = h < H;  // H is a multiple of 128: whole waves
+  const uint16_t* x = (const uint16_t*)a.x + (in ? h : 0);
+  const float* dzp = a.dz_pool + (a.soft ? a.n_pub : 0) + pe0;
+  float s[DWP_E][2];
+#pragma unroll
+  for (int e = 0; e < DWP_E; ++e) s[e][0] = s[e][1] = 0.f;
+  constexpr int U = 16;  // tokens in flight (those past the range reload its last token)
+  for (int tb = t0; tb < t1; tb += DWP_B) {
+    const int nb = min(DWP_B, t1 - tb);
+    __syncthreads();
+    for (int i = tid; i < nb * DWP_E; i += DWP_THREADS) {
+      const int t = i / DWP_E, e = i % DWP_E;  // experts past the pool: summed, never stored
+      s_dz[t][e] = dzp[(size_t)(tb + t) * a.pool_stride + (e < ne ? e : 0)];
+    }
+    if (tid < nb) s_mine[tid] = a.soft || a.topk_idx[(size_t)(tb + tid) * a.k] >= a.n_pub;
+    __syncthreads();
+    for (int ub = 0; ub < nb; ub += U) {
+      uint32_t v[U];
+#pragma unroll
+      for (int i = 0; i < U; ++i) v[i] = *(const uint32_t*)(x + (size_t)(tb + min(ub + i, nb - 1)) * H);
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        if (ub + i >= nb || !s_mine[ub + i]) continue;  // a public-pool token
+        const float x0 = bf16_to_f32(v[i] & 0xFFFFu), x1 = bf16_to_f32(v[i] >> 16);
+#pragma unroll
+        for (int e = 0; e < DWP_E; e += 4) {
+          const f32x4 d = *(const f32x4*)&s_dz[ub + i][e];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            s[e + q][0] += d[q] * x0;
+            s[e + q][1] += d[q] * x1;
+          }
+        }
+      }
+    }
+  }
+  if (!in) return;
+#pragma unroll
+  for (int e = 0; e < DWP_E; ++e) {
+    if (e >= ne) continue;
+    float* part = a.dwr_part + ((size_t)(pe0 + e) * BWD_DWR_SPLIT + c) * H + h;
+    part[0] = s[e][0];
+    part[1] = s[e][1];
   }
 }
 
@@ -628,8 +755,21 @@ hipError_t launch_backward(const BwdArgs& a, hipStream_t s) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (a.pool_gates) {
-    const size_t lds = ((size_t)H + a.pool_stride + 1) * sizeof(float);
-    bwd_pool_dz_kernel<<<a.T, BT, lds, s>>>(a);
+    // the pool logits again, by the forward's router kernel: split over H like the forward's
+    // where the partial arrays fit the row-input-gradient buffer (unused until the last
+    // products), else in one piece, straight into dz_pool
+    RouteArgs r{};
+    r.T = a.T; r.H = H; r.n_pub = a.n_pub; r.n_priv = a.n_priv; r.k = a.k; r.act_bf16 = 1;
+    r.x = a.x; r.wr_pub = a.wr_pub; r.wr_priv = a.wr_priv; r.bias = a.bias;
+    r.zstride = a.pool_stride; r.soft = a.soft; r.pool_idx = a.topk_idx;
+    // (the large-batch kernel copies whole 16-byte chunks of the router rows)
+    r.narrow = (((uintptr_t)a.wr_pub | (uintptr_t)a.wr_priv) & 15) != 0;
+    r.zsplit = r.narrow ? 1 : route_ksplit(a.T, H, a.n_pub, a.n_priv, 1);
+    if ((int64_t)r.zsplit * a.pool_stride > (int64_t)a.k * H) r.zsplit = 1;
+    r.z = r.zsplit > 1 ? a.dXr : a.dz_pool;
+    e = launch_route_logits(r, s);
+    if (e != hipSuccess) return e;
+    bwd_pool_dz_kernel<<<(a.T + BT / 64 - 1) / (BT / 64), BT, 0, s>>>(a, r.z, r.zsplit);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -770,7 +910,7 @@ hipError_t launch_backward(const BwdArgs& a, hipStream_t s) {
   }
   if (a.n_priv > 0) {
     if (a.pool_gates)
-      bwd_dwr_pool_part_kernel<<<dim3(a.n_priv, BWD_DWR_SPLIT), BT, 0, s>>>(a);
+      bwd_dwr_pool_part_kernel<<<dim3((H + DWP_H - 1) / DWP_H, BWD_DWR_SPLIT, (a.n_priv + DWP_E - 1) / DWP_E), DWP_THREADS, 0, s>>>(a);
     else
       bwd_dwr_part_kernel<<<dim3(a.n_priv, BWD_DWR_SPLIT), BT, 0, s>>>(a);
     e = hipGetLastError();
@@ -779,7 +919,12 @@ hipError_t launch_backward(const BwdArgs& a, hipStream_t s) {
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if (a.w2t_pub)
+  const int dxp = (a.T + DXP_T - 1) / DXP_T;
+  if (a.pool_gates && a.w2t_pub)
+    bwd_dx_pool_kernel<true><<<dxp, BT, 0, s>>>(a);
+  else if (a.pool_gates)
+    bwd_dx_pool_kernel<false><<<dxp, BT, 0, s>>>(a);
+  else if (a.w2t_pub)
     bwd_dx_kernel<true><<<a.T, BT, 0, s>>>(a);
   else
     bwd_dx_kernel<false><<<a.T, BT, 0, s>>>(a);

@@ -109,10 +109,15 @@ struct RouteArgs {
   int zstride;
   int soft;     // control arm: every token ranks the concatenated pool (z holds all E logits)
   int zsplit;   // partial logit arrays (K split of the logits); the top-k adds them in order
+  // the backward's recomputed logits: a token's pool is the one its first selected expert
+  // (pool_idx[t * k]) lies in, whatever the policy words
+  const int32_t* pool_idx = nullptr;
+  int narrow = 0;  // use the register kernel for any batch (zsplit 1)
 };
 // K splits of the router logits for a batch (1 unless the wide large-batch kernel runs);
 // the route workspace holds this many [T, zstride] fp32 arrays.
 int route_ksplit(int T, int H, int n_pub, int n_priv, int act_bf16);
+hipError_t launch_route_logits(const RouteArgs& a, hipStream_t s);  // z only
 hipError_t launch_route(const RouteArgs& a, hipStream_t s);
 
 struct DispatchArgs {

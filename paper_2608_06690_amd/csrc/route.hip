@@ -108,6 +108,7 @@ __device__ __forceinline__ void wave_bitonic_sort(uint64_t (&v)[NPL]) {
 // tau of token t: only the exact allow word allows; with no private router the token
 // fails closed to deny (and the status bit is raised).
 __device__ __forceinline__ int token_tau(const RouteArgs& a, int t) {
+  if (a.pool_idx) return a.pool_idx[(size_t)t * a.k] >= a.n_pub ? 1 : 0;
   int tau = (a.words != nullptr && a.words[t] == PMPE_POLICY_ALLOW) ? 1 : 0;
   if (tau == 1 && a.wr_priv == nullptr) {
     tau = 0;
@@ -573,9 +574,9 @@ int route_ksplit(int T, int H, int n_pub, int n_priv, int act_bf16) {
   return S;
 }
 
-hipError_t launch_route(const RouteArgs& a, hipStream_t s) {
+hipError_t launch_route_logits(const RouteArgs& a, hipStream_t s) {
   if (a.act_bf16) {
-    if (a.T > 2048) {
+    if (a.T > 2048 && !a.narrow) {
       const int nt = (a.T + RW_TT - 1) / RW_TT;
       const int groups = (a.n_pub + RW_NE - 1) / RW_NE + (a.n_priv + RW_NE - 1) / RW_NE;
       // 8 XCDs x ceil(nt / 8) tiles each x the groups and K splits of a tile
@@ -590,6 +591,12 @@ hipError_t launch_route(const RouteArgs& a, hipStream_t s) {
   } else {
     hipLaunchKernelGGL(route_logits_f32_kernel, dim3(a.T), dim3(RT_THREADS), 0, s, a);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_route(const RouteArgs& a, hipStream_t s) {
+  const hipError_t e = launch_route_logits(a, s);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(route_topk_kernel, dim3((a.T + RT_WAVES - 1) / RT_WAVES), dim3(RT_THREADS), 0, s, a);
   return hipGetLastError();
 }
