@@ -45,6 +45,17 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
   return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
+// The choose and majority functions (FIPS 180-4 4.1.2) as one such operation each (truth tables
+// over a = 0xF0, b = 0xCC, c = 0xAA). Spelled with and, xor and not, the majority compiled to
+// three operations, 128 of about 1,530 per block (1.15 GB of weights: 989 -> 889 us, with the
+// byte-wise padding of whole chunks skipped).
+__device__ __forceinline__ uint32_t choose(uint32_t e, uint32_t f, uint32_t g) {
+  return __builtin_amdgcn_bitop3_b32(e, f, g, 0xCA);
+}
+__device__ __forceinline__ uint32_t majority(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0xE8);
+}
+
 // One compression (FIPS 180-4 6.2.2) of the 16-word block w into state s. The message
 // schedule is kept as a rolling window of 16 words in w itself (w is overwritten).
 __device__ __forceinline__ void compress(uint32_t (&s)[8], uint32_t (&w)[16]) {
@@ -62,10 +73,10 @@ __device__ __forceinline__ void compress(uint32_t (&s)[8], uint32_t (&w)[16]) {
       w[t & 15] = wt;
     }
     const uint32_t S1 = xor3(rotr(e, 6), rotr(e, 11), rotr(e, 25));
-    const uint32_t ch = (e & f) ^ (~e & g);
+    const uint32_t ch = choose(e, f, g);
     const uint32_t t1 = h + S1 + ch + kRound[t] + wt;
     const uint32_t S0 = xor3(rotr(a, 2), rotr(a, 13), rotr(a, 22));
-    const uint32_t maj = (a & b) ^ (a & c) ^ (b & c);
+    const uint32_t maj = majority(a, b, c);
     const uint32_t t2 = S0 + maj;
     h = g;
     g = f;
@@ -121,17 +132,23 @@ __global__ __launch_bounds__(64) void sha256_chunks_kernel(const uint8_t* __rest
   // Padding (FIPS 180-4 5.1.1): the r = len mod 64 remaining bytes, one 0x80 byte, zeros,
   // then the message length in bits as a 64-bit big-endian integer in the last 8 bytes;
   // when r >= 56 the length spills into a second block.
+  // Whole chunks have no remaining byte; only the last chunk of a level may.
   const uint32_t r = len & 63u;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    uint32_t word = 0;
+  for (int i = 0; i < 16; ++i) w[i] = 0;
+  w[0] = 0x80000000u;
+  if (r > 0) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const uint32_t j = 4 * i + k;
-      const uint32_t byte = j < r ? (uint32_t)p[j] : (j == r ? 0x80u : 0u);
-      word |= byte << (24 - 8 * k);
+    for (int i = 0; i < 16; ++i) {
+      uint32_t word = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t j = 4 * i + k;
+        const uint32_t byte = j < r ? (uint32_t)p[j] : (j == r ? 0x80u : 0u);
+        word |= byte << (24 - 8 * k);
+      }
+      w[i] = word;
     }
-    w[i] = word;
   }
   const uint64_t bits = (uint64_t)len * 8;
   if (r >= 56) {
