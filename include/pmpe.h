@@ -301,6 +301,66 @@ pmpe_status pmpe_audit(const pmpe_layer_desc* d, int32_t T, const uint32_t* audi
                        uint32_t* deny_violations, pmpe_stream_t stream);
 
 /*
+ * pmpe_layer_forward - the five calls of one layer forward in order (route, dispatch,
+ * expert FFN, combine, audit), from one argument block: the same checks, kernels and
+ * results as the calls one by one, for callers whose batches are so small that the
+ * cost of making five calls shows (decode).
+ *
+ * Fields are named as in those calls. ffn selects the expert FFN call (PMPE_FFN_*; with
+ * PMPE_FFN_FP8 that call gets the descriptor with w_dtype = PMPE_FP8_E4M3, the others `d`
+ * as it is); req_offset NULL: no audit call. The block is a host structure read during the
+ * call only. Returns the first failing call's status, with `failed` set to its position (0
+ * route .. 4 audit); the calls before it have been launched. PMPE_ERR_NULL when d or args
+ * is NULL, PMPE_ERR_SHAPE for another ffn value.
+ */
+typedef enum { PMPE_FFN_PLAIN = 0, PMPE_FFN_TRAIN = 1, PMPE_FFN_FP8 = 2 } pmpe_ffn_kind;
+typedef struct {
+  const void* x;
+  const float* wr_pub;
+  const float* wr_priv;
+  const float* logit_bias;
+  const uint32_t* policy_word;
+  int32_t* topk_idx;
+  float* topk_gate;
+  uint8_t* allow;
+  float* kgap;
+  int32_t* expert_count;
+  int32_t* expert_offset;
+  int32_t* row_token;
+  int32_t* token_row;
+  void* x_perm;
+  const void* w13_pub;
+  const void* w2_pub;
+  const void* w13_priv;
+  const void* w2_priv;
+  const void* w13_sh;
+  const void* w2_sh;
+  const float* w13s_pub;
+  const float* w2s_pub;
+  const float* w13s_priv;
+  const float* w2s_priv;
+  void* y_shared;
+  void* y_perm;
+  float* ab;
+  void* out;
+  uint32_t* audit_token_rows;
+  uint32_t* audit_priv_calls;
+  const int32_t* req_offset;
+  uint64_t* req_private_rows;
+  uint64_t* total_private_rows;
+  uint32_t* deny_violations;
+  uint32_t* dev_status;
+  void* ws;
+  size_t ws_bytes;
+  int32_t R;      /* requests of req_offset */
+  int32_t ffn;    /* pmpe_ffn_kind */
+  int32_t failed; /* out */
+} pmpe_forward_args;
+
+pmpe_status pmpe_layer_forward(const pmpe_layer_desc* d, int32_t T, pmpe_forward_args* args,
+                               pmpe_stream_t stream);
+
+/*
  * pmpe_expert_ffn_fp8 - pmpe_expert_ffn with expert weights stored as fp8 (OCP e4m3) and
  * one fp32 scale per weight row that is a power of two: the weight is q * scale. A
  * precision variant (the paper's models ran in bf16); activations, accumulation and

@@ -85,6 +85,18 @@ def make_cache_tag(decision: int, model_revision: bytes, checkpoint_fingerprint:
     return t
 
 
+class ForwardArgs(ctypes.Structure):
+    """pmpe_forward_args: the buffers of one layer forward."""
+    POINTERS = (
+        "x", "wr_pub", "wr_priv", "logit_bias", "policy_word", "topk_idx", "topk_gate", "allow", "kgap",
+        "expert_count", "expert_offset", "row_token", "token_row", "x_perm", "w13_pub", "w2_pub", "w13_priv",
+        "w2_priv", "w13_sh", "w2_sh", "w13s_pub", "w2s_pub", "w13s_priv", "w2s_priv", "y_shared", "y_perm", "ab",
+        "out", "audit_token_rows", "audit_priv_calls", "req_offset", "req_private_rows", "total_private_rows",
+        "deny_violations", "dev_status", "ws")
+    _fields_ = [(n, ctypes.c_void_p) for n in POINTERS] + [
+        ("ws_bytes", ctypes.c_size_t), ("R", ctypes.c_int32), ("ffn", ctypes.c_int32), ("failed", ctypes.c_int32)]
+
+
 _P = ctypes.c_void_p
 _I32 = ctypes.c_int32
 _SZ = ctypes.c_size_t
@@ -110,6 +122,9 @@ _lib.pmpe_combine.restype = _I32
 _lib.pmpe_combine.argtypes = [_DESC, _I32] + [_P] * 5 + [_P]
 _lib.pmpe_audit.restype = _I32
 _lib.pmpe_audit.argtypes = [_DESC, _I32, _P, _P, _P, _I32, _P, _P, _P, _P]
+
+_lib.pmpe_layer_forward.restype = _I32
+_lib.pmpe_layer_forward.argtypes = [_DESC, _I32, ctypes.POINTER(ForwardArgs), _P]
 
 _lib.pmpe_backward_workspace_bytes.restype = _SZ
 _lib.pmpe_backward_workspace_bytes.argtypes = [_DESC, _I32]
@@ -142,7 +157,7 @@ EXPORTED = ["pmpe_version", "pmpe_status_string", "pmpe_workspace_bytes", "pmpe_
             "pmpe_fingerprint_workspace_bytes", "pmpe_fingerprint", "pmpe_backward_workspace_bytes",
             "pmpe_backward", "pmpe_expert_ffn_train", "pmpe_route_record", "pmpe_cache_tag_check",
             "pmpe_expert_ffn_lora_workspace_bytes", "pmpe_expert_ffn_lora", "pmpe_adamw",
-            "pmpe_transpose_experts", "pmpe_expert_ffn_fp8"]
+            "pmpe_transpose_experts", "pmpe_expert_ffn_fp8", "pmpe_layer_forward"]
 
 PMPE_FP_LEAF_BYTES = 1024
 PMPE_FP_FANOUT = 16
@@ -238,6 +253,24 @@ def pmpe_audit(desc, T, audit_token_rows, allow, req_offset, R, req_private_rows
     _check(_lib.pmpe_audit(ctypes.byref(desc), T, _ptr(audit_token_rows), _ptr(allow),
                            _ptr(req_offset), R, _ptr(req_private_rows), _ptr(total_private_rows),
                            _ptr(deny_violations), _stream(stream)), "pmpe_audit")
+
+
+PMPE_FFN_PLAIN = 0
+PMPE_FFN_TRAIN = 1
+PMPE_FFN_FP8 = 2
+_FFN_CALLS = ("pmpe_expert_ffn", "pmpe_expert_ffn_train", "pmpe_expert_ffn_fp8")
+
+
+def pmpe_layer_forward(desc, T, tensors, R, ffn=PMPE_FFN_PLAIN, stream=None) -> None:
+    """The five calls of a layer forward in one: `tensors` in the order of
+    ForwardArgs.POINTERS (None where the C call takes NULL). An error names the call."""
+    ptrs = [None if t is None else t.data_ptr() if t.is_contiguous() else _ptr(t) for t in tensors]
+    ws = tensors[-1]
+    a = ForwardArgs(*ptrs, 0 if ws is None else ws.numel() * ws.element_size(), R, ffn, 0)
+    status = _lib.pmpe_layer_forward(ctypes.byref(desc), T, ctypes.byref(a), _stream(stream))
+    if status != PMPE_OK:
+        raise PmpeError(status, ("pmpe_route", "pmpe_dispatch", _FFN_CALLS[ffn], "pmpe_combine",
+                                 "pmpe_audit")[a.failed])
 
 
 def pmpe_backward_workspace_bytes(desc: LayerDesc, T: int) -> int:

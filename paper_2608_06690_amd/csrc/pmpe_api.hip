@@ -475,6 +475,46 @@ pmpe_status pmpe_backward(const pmpe_layer_desc* d, int32_t T, const void* x, co
   return launched(launch_backward(a, (hipStream_t)stream));
 }
 
+pmpe_status pmpe_layer_forward(const pmpe_layer_desc* d, int32_t T, pmpe_forward_args* args,
+                               pmpe_stream_t stream) {
+  if (d == nullptr || args == nullptr) return PMPE_ERR_NULL;
+  const pmpe_forward_args& a = *args;
+  args->failed = 0;
+  if (a.ffn < PMPE_FFN_PLAIN || a.ffn > PMPE_FFN_FP8) return PMPE_ERR_SHAPE;
+  pmpe_status st = pmpe_route(d, T, a.x, a.wr_pub, a.wr_priv, a.logit_bias, a.policy_word, a.topk_idx, a.topk_gate,
+                              a.allow, a.kgap, a.dev_status, a.ws, a.ws_bytes, stream);
+  if (st != PMPE_OK) return st;
+  args->failed = 1;
+  st = pmpe_dispatch(d, T, a.topk_idx, a.x, a.expert_count, a.expert_offset, a.row_token, a.token_row, a.x_perm, a.ws,
+                     a.ws_bytes, stream);
+  if (st != PMPE_OK) return st;
+  args->failed = 2;
+  if (a.ffn == PMPE_FFN_FP8) {
+    pmpe_layer_desc d8 = *d;
+    d8.w_dtype = PMPE_FP8_E4M3;
+    st = pmpe_expert_ffn_fp8(&d8, T, a.x_perm, a.x, a.expert_count, a.expert_offset, a.row_token, a.w13_pub, a.w2_pub,
+                             a.w13_priv, a.w2_priv, a.w13s_pub, a.w2s_pub, a.w13s_priv, a.w2s_priv, a.y_perm,
+                             a.audit_token_rows, a.audit_priv_calls, a.dev_status, a.ws, a.ws_bytes, stream);
+  } else if (a.ffn == PMPE_FFN_TRAIN) {
+    st = pmpe_expert_ffn_train(d, T, a.x_perm, a.x, a.expert_count, a.expert_offset, a.row_token, a.w13_pub, a.w2_pub,
+                               a.w13_priv, a.w2_priv, a.w13_sh, a.w2_sh, a.y_shared, a.y_perm, a.audit_token_rows,
+                               a.audit_priv_calls, a.dev_status, a.ab, a.ws, a.ws_bytes, stream);
+  } else {
+    st = pmpe_expert_ffn(d, T, a.x_perm, a.x, a.expert_count, a.expert_offset, a.row_token, a.w13_pub, a.w2_pub,
+                         a.w13_priv, a.w2_priv, a.w13_sh, a.w2_sh, a.y_shared, a.y_perm, a.audit_token_rows,
+                         a.audit_priv_calls, a.dev_status, a.ws, a.ws_bytes, stream);
+  }
+  if (st != PMPE_OK) return st;
+  args->failed = 3;
+  st = pmpe_combine(d, T, a.y_perm, a.token_row, a.topk_gate, a.y_shared, a.out, stream);
+  if (st != PMPE_OK) return st;
+  args->failed = 4;
+  if (a.req_offset)
+    st = pmpe_audit(d, T, a.audit_token_rows, a.allow, a.req_offset, a.R, a.req_private_rows, a.total_private_rows,
+                    a.deny_violations, stream);
+  return st;
+}
+
 pmpe_status pmpe_adamw(void* param, int32_t param_dtype, float* master, const float* grad,
                        float* m, float* v, uint64_t n, int32_t step, float lr, float beta1,
                        float beta2, float eps, float weight_decay, pmpe_stream_t stream) {

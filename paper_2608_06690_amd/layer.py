@@ -47,12 +47,24 @@ class AuditBuffers:
     req_rows: torch.Tensor      # [R] uint64 (int64 storage)
     total: torch.Tensor         # [1]
     violations: torch.Tensor    # [1]
+    # token_rows and priv_calls in one tensor, when they were allocated so
+    counters: Optional[torch.Tensor] = None
 
     def zero_(self) -> "AuditBuffers":
-        # fill kernels (torch's zero_), not memset nodes
-        self.token_rows.zero_()
-        self.priv_calls.zero_()
+        # fill kernels (torch's zero_), not memset nodes; one for both counters when they are
+        # (still) the two parts of one tensor
+        c = self.counters
+        if (c is not None and c.data_ptr() == self.token_rows.data_ptr()
+                and c.numel() == self.token_rows.numel() + self.priv_calls.numel()
+                and self.priv_calls.data_ptr() == c.data_ptr() + 4 * self.token_rows.numel()):
+            c.zero_()
+        else:
+            self.token_rows.zero_()
+            self.priv_calls.zero_()
         return self
+
+
+_STEPS = frozenset(("route", "dispatch", "expert_ffn", "combine", "audit"))
 
 
 class PolicyMaskedMoE:
@@ -104,11 +116,11 @@ class PolicyMaskedMoE:
 
     def audit_buffers(self, T: int, R: int) -> AuditBuffers:
         dev = self.device
-        return AuditBuffers(torch.zeros(T, dtype=torch.int32, device=dev),
-                            torch.zeros(self.desc.n_priv, dtype=torch.int32, device=dev),
+        c = torch.zeros(T + self.desc.n_priv, dtype=torch.int32, device=dev)
+        return AuditBuffers(c[:T], c[T:],
                             torch.zeros(R, dtype=torch.int64, device=dev),
                             torch.zeros(1, dtype=torch.int64, device=dev),
-                            torch.zeros(1, dtype=torch.int32, device=dev))
+                            torch.zeros(1, dtype=torch.int32, device=dev), c)
 
     def route(self, x, words, b: LayerBuffers, stream=None):
         T = x.shape[0]
@@ -123,9 +135,7 @@ class PolicyMaskedMoE:
     def expert_ffn(self, x, b: LayerBuffers, audit: AuditBuffers, stream=None, train=False):
         T = x.shape[0]
         if train:
-            if b.ab is None:
-                b.ab = torch.empty(T * self.desc.top_k, 2 * self.desc.inter, dtype=torch.float32,
-                                   device=self.device)
+            self._train_buffers(b, T)
             N.pmpe_expert_ffn_train(
                 self.desc, T, b.x_perm, x, b.expert_count, b.expert_offset, b.row_token,
                 self.w13_pub, self.w2_pub, self.w13_priv, self.w2_priv, self.w13_sh, self.w2_sh,
@@ -136,6 +146,31 @@ class PolicyMaskedMoE:
                           self.w13_pub, self.w2_pub, self.w13_priv, self.w2_priv, self.w13_sh,
                           self.w2_sh, b.y_shared, b.y_perm, audit.token_rows, audit.priv_calls,
                           b.dev_status, b.ws, stream)
+
+    def _train_buffers(self, b: LayerBuffers, T: int) -> None:
+        if b.ab is None:
+            b.ab = torch.empty(T * self.desc.top_k, 2 * self.desc.inter, dtype=torch.float32,
+                               device=self.device)
+
+    def _plain_steps(self) -> bool:
+        # the steps are this class's own: a subclass or an object that replaces one of them
+        # gets the calls one by one
+        return type(self) is PolicyMaskedMoE and _STEPS.isdisjoint(self.__dict__)
+
+    def _forward(self, x, words, b: LayerBuffers, audit: AuditBuffers, req_offset, stream, ffn: int,
+                 fp8=None) -> None:
+        """The five steps in one native call."""
+        if fp8 is None:
+            w = (self.w13_pub, self.w2_pub, self.w13_priv, self.w2_priv, self.w13_sh, self.w2_sh, None, None, None, None)
+        else:
+            w = (*fp8[:4], None, None, *fp8[4:])
+        N.pmpe_layer_forward(
+            self.desc, x.shape[0],
+            (x, self.wr_pub, self.wr_priv, self.bias, words, b.topk_idx, b.topk_gate, b.allow, b.kgap, b.expert_count,
+             b.expert_offset, b.row_token, b.token_row, b.x_perm, *w, b.y_shared, b.y_perm,
+             b.ab if ffn == N.PMPE_FFN_TRAIN else None, b.out, audit.token_rows,
+             audit.priv_calls, req_offset, audit.req_rows, audit.total, audit.violations, b.dev_status, b.ws),
+            0 if req_offset is None else req_offset.numel() - 1, ffn, stream)
 
     def combine(self, x, b: LayerBuffers, stream=None):
         T = x.shape[0]
@@ -169,6 +204,9 @@ class PolicyMaskedMoE:
         dispatch, combine and audit as in forward()."""
         T = x.shape[0]
         b = self.buffers(T)
+        if self._plain_steps():
+            self._forward(x, words, b, audit, req_offset, stream, N.PMPE_FFN_FP8, fp8)
+            return b
         self.route(x, words, b, stream)
         self.dispatch(x, b, stream)
         d8 = N.LayerDesc(*[getattr(self.desc, f) for f, _ in N.LayerDesc._fields_])
@@ -266,6 +304,11 @@ class PolicyMaskedMoE:
         """Runs the layer; returns the buffers (out, route log, dispatch) of this T. A
         training forward also keeps what the backward needs (b.ab)."""
         b = self.buffers(x.shape[0])
+        if self._plain_steps():
+            if train:
+                self._train_buffers(b, x.shape[0])
+            self._forward(x, words, b, audit, req_offset, stream, N.PMPE_FFN_TRAIN if train else N.PMPE_FFN_PLAIN)
+            return b
         self.route(x, words, b, stream)
         self.dispatch(x, b, stream)
         self.expert_ffn(x, b, audit, stream, train)

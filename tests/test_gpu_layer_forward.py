@@ -1,0 +1,75 @@
+"""The layer forward in one native call against the steps one by one: the same bits for each
+expert FFN, and the failing step named."""
+import dataclasses
+
+import pytest
+import torch
+
+import paper_2608_06690_amd as P
+from paper_2608_06690_amd import _native as N
+import workloads as W
+from tests import pmpe_cases as C
+
+pytestmark = pytest.mark.gpu
+
+
+class StepByStep(P.PolicyMaskedMoE):  # a subclass gets the calls one by one
+    pass
+
+
+def make(cls, cfg, Lw):
+    return cls(C.make_desc(cfg), Lw.wr_pub, Lw.wr_priv, Lw.bias, Lw.w13_pub, Lw.w2_pub, Lw.w13_priv, Lw.w2_priv,
+               Lw.w13_sh, Lw.w2_sh)
+
+
+@pytest.mark.parametrize("kind", ["plain", "train", "fp8", "shared", "f32", "no_audit"])
+def test_one_call_equals_the_steps(kind):
+    cfg = W.scaled_config(W.get_config("deepseek" if kind == "shared" else "qwen"), tokens=70, requests=5, hidden=256,
+                          inter=128, n_pub=12, n_priv=9, top_k=3, dtype="f32" if kind == "f32" else "bf16",
+                          shared_inter=128 if kind == "shared" else 0)
+    Lw = W.make_layer(cfg, 0, "cuda")
+    x = W.make_x(cfg, "cuda")
+    words = torch.where(torch.arange(cfg.tokens, device="cuda") % 3 == 0,
+                        torch.tensor(P.PMPE_POLICY_ALLOW - 2**32, device="cuda"), 0).to(torch.int32)
+    off = None if kind == "no_audit" else torch.tensor([0, 7, 7, 30, 69, 70], dtype=torch.int32, device="cuda")
+    fp8 = None
+    if kind == "fp8":
+        q = {n: W.quantize_fp8_rows(getattr(Lw, n)) for n in ("w13_pub", "w2_pub", "w13_priv", "w2_priv")}
+        fp8 = tuple(q[n][0] for n in q) + tuple(q[n][1] for n in q)
+    got = []
+    for cls in (P.PolicyMaskedMoE, StepByStep):
+        layer = make(cls, cfg, Lw)
+        audit = layer.audit_buffers(cfg.tokens, 5)
+        for _ in range(2):  # counters accumulate until they are zeroed
+            audit.zero_()
+            b = (layer.forward_fp8(x, words, fp8, audit, off) if fp8 else
+                 layer.forward(x, words, audit, off, train=kind == "train"))
+        t = [b.out, b.topk_idx, b.topk_gate, b.allow, b.kgap, b.expert_count, b.row_token, b.token_row, b.y_perm,
+             audit.token_rows, audit.priv_calls, audit.req_rows, audit.total, audit.violations]
+        got.append([v.clone() for v in t + ([b.ab] if kind == "train" else [])])
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    assert int(got[0][9].sum()) > 0
+
+
+def test_failing_step_is_named():
+    cfg = W.scaled_config(W.get_config("qwen"), tokens=16, requests=2, hidden=128, inter=64, n_pub=4, n_priv=4, top_k=2)
+    layer = make(P.PolicyMaskedMoE, cfg, W.make_layer(cfg, 0, "cuda"))
+    x, words = W.make_x(cfg, "cuda"), torch.zeros(16, dtype=torch.int32, device="cuda")
+    audit = layer.audit_buffers(16, 1)
+    b = layer.buffers(16)
+    full = b.ws
+    b.ws = full[:16 * 4 * 4]  # enough for the router only
+    with pytest.raises(P.PmpeError, match="pmpe_dispatch"):
+        layer.forward(x, words, audit)
+    b.ws = full[:0]
+    with pytest.raises(P.PmpeError, match="pmpe_route"):
+        layer.forward(x, words, audit)
+    b.ws = full
+    with pytest.raises(P.PmpeError, match="pmpe_expert_ffn_fp8"):
+        layer.forward_fp8(x, words, (layer.w13_pub, layer.w2_pub, None, None, None, None, None, None), audit)
+    with pytest.raises(ValueError):
+        layer.forward(x.t().contiguous().t(), words, audit)
+    replaced = dataclasses.replace(audit, token_rows=torch.ones(16, dtype=torch.int32, device="cuda"))
+    replaced.zero_()
+    assert int(replaced.token_rows.sum()) == 0
+    assert N.pmpe_version() == 10000
