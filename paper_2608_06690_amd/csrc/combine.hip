@@ -5,7 +5,11 @@
 // sum runs in fp32 in slot order j = 0..k-1 and is rounded once, which makes the
 // output bitwise deterministic (no atomics). Slots with token_row = -1 (an invalid
 // expert id upstream) contribute nothing.
-#include "pmpe_internal.h"
+//
+// In a layer forward an extra first block runs the audit reduce (aud.total != NULL): it needs
+// only the expert FFN's counters, so it finishes beside the combine instead of after it
+// (3 to 11 us of a launch of its own).
+#include "audit_block.h"
 
 namespace pmpe {
 namespace {
@@ -16,8 +20,12 @@ constexpr int CB_THREADS = 256;
 // together (rows and gates first, then every slot's 16-byte vector) before the sum;
 // KC == 0: any k, one slot at a time. Both add the slots in the same order.
 template <int KC>
-__global__ __launch_bounds__(CB_THREADS) void combine_bf16_kernel(CombineArgs a) {
-  const int t = blockIdx.x;
+__global__ __launch_bounds__(CB_THREADS) void combine_bf16_kernel(CombineArgs a, AuditArgs aud) {
+  if (aud.total && blockIdx.x == 0) {
+    audit_block<CB_THREADS / 64>(aud);
+    return;
+  }
+  const int t = aud.total ? blockIdx.x - 1 : blockIdx.x;
   const int H = a.H;
   const uint16_t* yp = (const uint16_t*)a.y_perm;
   const uint16_t* ysh = (const uint16_t*)a.y_shared;
@@ -75,8 +83,12 @@ __global__ __launch_bounds__(CB_THREADS) void combine_bf16_kernel(CombineArgs a)
   }
 }
 
-__global__ __launch_bounds__(CB_THREADS) void combine_f32_kernel(CombineArgs a) {
-  const int t = blockIdx.x;
+__global__ __launch_bounds__(CB_THREADS) void combine_f32_kernel(CombineArgs a, AuditArgs aud) {
+  if (aud.total && blockIdx.x == 0) {
+    audit_block<CB_THREADS / 64>(aud);
+    return;
+  }
+  const int t = aud.total ? blockIdx.x - 1 : blockIdx.x;
   const int H = a.H;
   const float* yp = (const float*)a.y_perm;
   const float* ysh = (const float*)a.y_shared;
@@ -106,16 +118,19 @@ __global__ __launch_bounds__(CB_THREADS) void combine_f32_kernel(CombineArgs a) 
 
 }  // namespace
 
-hipError_t launch_combine(const CombineArgs& a, hipStream_t s) {
+hipError_t launch_combine(const CombineArgs& a, hipStream_t s, const AuditArgs* audit) {
+  const AuditArgs au = audit ? *audit : AuditArgs{};
+  const dim3 grid((unsigned)a.T + (audit ? 1 : 0));
   if (a.act_bf16) {
     switch (a.k) {
-      case 2: hipLaunchKernelGGL(combine_bf16_kernel<2>, dim3(a.T), dim3(CB_THREADS), 0, s, a); break;
-      case 6: hipLaunchKernelGGL(combine_bf16_kernel<6>, dim3(a.T), dim3(CB_THREADS), 0, s, a); break;
-      case 8: hipLaunchKernelGGL(combine_bf16_kernel<8>, dim3(a.T), dim3(CB_THREADS), 0, s, a); break;
-      default: hipLaunchKernelGGL(combine_bf16_kernel<0>, dim3(a.T), dim3(CB_THREADS), 0, s, a); break;
+      case 2: hipLaunchKernelGGL(combine_bf16_kernel<2>, grid, dim3(CB_THREADS), 0, s, a, au); break;
+      case 6: hipLaunchKernelGGL(combine_bf16_kernel<6>, grid, dim3(CB_THREADS), 0, s, a, au); break;
+      case 8: hipLaunchKernelGGL(combine_bf16_kernel<8>, grid, dim3(CB_THREADS), 0, s, a, au); break;
+      default: hipLaunchKernelGGL(combine_bf16_kernel<0>, grid, dim3(CB_THREADS), 0, s, a, au); break;
     }
-  } else
-    hipLaunchKernelGGL(combine_f32_kernel, dim3(a.T), dim3(CB_THREADS), 0, s, a);
+  } else {
+    hipLaunchKernelGGL(combine_f32_kernel, grid, dim3(CB_THREADS), 0, s, a, au);
+  }
   return hipGetLastError();
 }
 

@@ -175,6 +175,31 @@ pmpe_status expert_ffn_impl(const pmpe_layer_desc* d, int32_t T, const void* x_p
   return launched(launch_expert_ffn(a, (hipStream_t)stream));
 }
 
+// pmpe_combine; with `audit` (checked) and T > 0 its launch also runs the audit reduce
+pmpe_status combine_impl(const pmpe_layer_desc* d, int32_t T, const void* y_perm,
+                         const int32_t* token_row, const float* topk_gate, const void* y_shared,
+                         void* out, pmpe_stream_t stream, const AuditArgs* audit) {
+  pmpe_status st = check_desc(d, T);
+  if (st != PMPE_OK) return st;
+  if (!y_perm || !token_row || !topk_gate || !out) return PMPE_ERR_NULL;
+  if (d->n_shared > 0 && !y_shared) return PMPE_ERR_NULL;
+  if (!aligned16(y_perm) || !aligned16(out) || (y_shared && !aligned16(y_shared))) return PMPE_ERR_ALIGN;
+  if (T == 0) return PMPE_OK;
+  CombineArgs a{T, d->hidden, d->top_k, d->act_dtype == PMPE_BF16, y_perm, token_row,
+                topk_gate, d->n_shared > 0 ? y_shared : nullptr, out};
+  return launched(launch_combine(a, (hipStream_t)stream, audit));
+}
+
+pmpe_status check_audit(const pmpe_layer_desc* d, const AuditArgs& a) {
+  pmpe_status st = check_desc(d, a.T);
+  if (st != PMPE_OK) return st;
+  if (a.R < 0 || a.R > PMPE_MAX_TOKENS) return PMPE_ERR_SHAPE;
+  if (!a.total || !a.violations) return PMPE_ERR_NULL;
+  if (a.T > 0 && (!a.rows || !a.allow)) return PMPE_ERR_NULL;
+  if (a.R > 0 && (!a.req_offset || !a.req_rows)) return PMPE_ERR_NULL;
+  return PMPE_OK;
+}
+
 }  // namespace
 
 namespace pmpe {
@@ -282,30 +307,17 @@ pmpe_status pmpe_expert_ffn_train(const pmpe_layer_desc* d, int32_t T, const voi
 pmpe_status pmpe_combine(const pmpe_layer_desc* d, int32_t T, const void* y_perm,
                          const int32_t* token_row, const float* topk_gate,
                          const void* y_shared, void* out, pmpe_stream_t stream) {
-  pmpe_status st = check_desc(d, T);
-  if (st != PMPE_OK) return st;
-  if (!y_perm || !token_row || !topk_gate || !out) return PMPE_ERR_NULL;
-  if (d->n_shared > 0 && !y_shared) return PMPE_ERR_NULL;
-  if (!aligned16(y_perm) || !aligned16(out) || (y_shared && !aligned16(y_shared))) return PMPE_ERR_ALIGN;
-  if (T == 0) return PMPE_OK;
-  CombineArgs a{T, d->hidden, d->top_k, d->act_dtype == PMPE_BF16, y_perm, token_row,
-                topk_gate, d->n_shared > 0 ? y_shared : nullptr, out};
-  return launched(launch_combine(a, (hipStream_t)stream));
+  return combine_impl(d, T, y_perm, token_row, topk_gate, y_shared, out, stream, nullptr);
 }
 
 pmpe_status pmpe_audit(const pmpe_layer_desc* d, int32_t T, const uint32_t* audit_token_rows,
                        const uint8_t* allow, const int32_t* req_offset, int32_t R,
                        uint64_t* req_private_rows, uint64_t* total_private_rows,
                        uint32_t* deny_violations, pmpe_stream_t stream) {
-  pmpe_status st = check_desc(d, T);
-  if (st != PMPE_OK) return st;
-  if (R < 0 || R > PMPE_MAX_TOKENS) return PMPE_ERR_SHAPE;
-  if (!total_private_rows || !deny_violations) return PMPE_ERR_NULL;
-  if (T > 0 && (!audit_token_rows || !allow)) return PMPE_ERR_NULL;
-  if (R > 0 && (!req_offset || !req_private_rows)) return PMPE_ERR_NULL;
   AuditArgs a{T, R, audit_token_rows, allow, req_offset, req_private_rows, total_private_rows,
               deny_violations};
-  return launched(launch_audit(a, (hipStream_t)stream));
+  const pmpe_status st = check_audit(d, a);
+  return st != PMPE_OK ? st : launched(launch_audit(a, (hipStream_t)stream));
 }
 
 pmpe_status pmpe_expert_ffn_fp8(const pmpe_layer_desc* d, int32_t T, const void* x_perm,
@@ -506,12 +518,16 @@ pmpe_status pmpe_layer_forward(const pmpe_layer_desc* d, int32_t T, pmpe_forward
   }
   if (st != PMPE_OK) return st;
   args->failed = 3;
-  st = pmpe_combine(d, T, a.y_perm, a.token_row, a.topk_gate, a.y_shared, a.out, stream);
+  // the audit reduce runs beside the combine, in the same launch, unless its arguments fail
+  const AuditArgs au{T, a.R, a.audit_token_rows, a.allow, a.req_offset, a.req_private_rows, a.total_private_rows,
+                     a.deny_violations};
+  const pmpe_status st_audit = a.req_offset ? check_audit(d, au) : PMPE_OK;
+  const bool fused = a.req_offset && st_audit == PMPE_OK && T > 0;
+  st = combine_impl(d, T, a.y_perm, a.token_row, a.topk_gate, a.y_shared, a.out, stream, fused ? &au : nullptr);
   if (st != PMPE_OK) return st;
   args->failed = 4;
-  if (a.req_offset)
-    st = pmpe_audit(d, T, a.audit_token_rows, a.allow, a.req_offset, a.R, a.req_private_rows, a.total_private_rows,
-                    a.deny_violations, stream);
+  st = st_audit;
+  if (st == PMPE_OK && a.req_offset && !fused) st = launched(launch_audit(au, (hipStream_t)stream));
   return st;
 }
 

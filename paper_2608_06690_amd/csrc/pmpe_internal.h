@@ -205,8 +205,6 @@ struct CombineArgs {
   const void* y_shared;
   void* out;
 };
-hipError_t launch_combine(const CombineArgs& a, hipStream_t s);
-
 struct AuditArgs {
   int T, R;
   const uint32_t* rows;
@@ -217,6 +215,8 @@ struct AuditArgs {
   uint32_t* violations;
 };
 hipError_t launch_audit(const AuditArgs& a, hipStream_t s);
+// with `audit` (T > 0), the audit reduce runs in an extra block of the combine
+hipError_t launch_combine(const CombineArgs& a, hipStream_t s, const AuditArgs* audit = nullptr);
 
 struct AdamwArgs {
   void* param;          // fp32, or bf16 when master is given
