@@ -35,8 +35,9 @@
 // copies issued in a burst stall the wave that issues them: one copy after every fourth to
 // eighth MFMA of the multiplying wave (1,245 -> 1,189 us) beats the reading wave issuing them.
 // Against one two-stage ring drained at every step (the previous kernel): 16384-token layer
-// 1,466 -> 1,330 us, DeepSeek-V2-Lite-shaped 8192-token layer 1,307 -> 1,253 us,
-// Qwen3-30B-A3B-shaped 4096-token layer 558 -> 535 us.
+// 1,466 -> 1,320 us, DeepSeek-V2-Lite-shaped 8192-token layer 1,307 -> 1,230 us,
+// Qwen3-30B-A3B-shaped 4096-token layer 558 -> 522 us (of it the last weight half tile of a
+// step without A1 between the MFMAs: expert FFN 471 -> 464 us).
 #include "lds_dma.h"
 #include "pmpe_internal.h"
 
@@ -84,7 +85,7 @@ __global__ __launch_bounds__(THREADS) void gemm256_kernel(FfnArgs a) {
   // they follow the copies of (S2..S4) and after that step (S5); for a tile without A1: S2, S5.
   constexpr int SQ = GATED ? (SAVE ? 5 : 1) : 1;  // per 16-row block and output half
   constexpr int S2 = GATED ? 0 : 4, S3 = GATED ? 2 * SQ : 4, S4 = GATED ? 2 * SQ : 4, S5 = 4 * SQ;
-  constexpr int SALL = S2 + S3 + S4 + S5, SHALF = S2 + S5;
+  constexpr int SALL = S2 + S3 + S4 + S5;
   __shared__ __attribute__((aligned(16))) unsigned char smem[2 * STEP];
   __shared__ __attribute__((aligned(16))) int s_rt[NRT][BM];
   __shared__ __attribute__((aligned(16))) int4 s_list[LIST];
@@ -374,12 +375,12 @@ __global__ __launch_bounds__(THREADS) void gemm256_kernel(FfnArgs a) {
       if (last)
         wait_vmcnt<N2 + SL>();
       else
-        wait_copies(ic<N2>, ic<S4 + S5>, ic<SHALF>, fresh == 2);
+        wait_copies(ic<N2>, ic<S4 + S5>, ic<S5>, fresh == 2);
     } else {
       if (last)
         wait_vmcnt<N2 - 4 + SL>();
       else
-        wait_copies(ic<N2 - 4>, ic<S5>, ic<SHALF>, fresh == 2);
+        wait_copies(ic<N2 - 4>, ic<S5>, ic<S5>, fresh == 2);
     }
   };
   // reads of this phase are done, and the waits above hold for every wave of the block
@@ -495,7 +496,7 @@ __global__ __launch_bounds__(THREADS) void gemm256_kernel(FfnArgs a) {
         readB(h0, fb0);
         // B1 of this step landed; younger: its A1 and the next step
         if (kind1)
-          wait_copies(ic<8>, ic<S5>, ic<SHALF>, fresh > 0);
+          wait_copies(ic<8>, ic<S5>, ic<S5>, fresh > 0);
         else
           wait_vmcnt<2>();
         phase_mid();
@@ -509,7 +510,7 @@ __global__ __launch_bounds__(THREADS) void gemm256_kernel(FfnArgs a) {
           if (last) store(h0, h0, ic<0>, ic<4>);
         // A1 of this step landed; younger: the next step
         if (kind1 == 2)
-          wait_copies(ic<8>, ic<SALL>, ic<SHALF>, fresh == 2);
+          wait_copies(ic<8>, ic<SALL>, ic<S5>, fresh == 2);
         else if (kind1 == 1)
           wait_vmcnt<6>();
         else
@@ -552,13 +553,18 @@ __global__ __launch_bounds__(THREADS) void gemm256_kernel(FfnArgs a) {
         phase_mid();
         if constexpr (AH == 1) mul(acc[0][0], fb0);
         phase_end();
-        kind2 = copy_step(cbuf);
+        kind2 = next_step();
+        if (kind2) {
+          copyA(h0, cbuf);
+          copyB(h0, cbuf);
+        }
         late = kind2 == 2;
         if constexpr (AH == 1 && !GATED)
           if (last) store(h0, h0, ic<0>, ic<4>);
-        wait_next(ic<AH == 1 ? S2 : 0>, last, ic<10>);
+        wait_next(ic<AH == 1 ? S2 : 0>, last, ic<8>);
         phase_mid();
-        if constexpr (AH == 1) mul(acc[0][1], fb1);
+        if constexpr (AH == 1) mulc(acc[0][1], fb1, [&](auto i) { if (kind2) copyB1(h1, i, cbuf); });
+        else if (kind2) copyB(h1, cbuf);
         phase_end();
         if constexpr (AH == 1)
           if (last) store(h0, ic<GATED ? 0 : 1>, ic<0>, ic<4>);
