@@ -43,9 +43,9 @@ COPY_BYTES = 1 << 30
 # for a plain copy of known size). Keyed by the SHA-256 of the kernel sources the
 # counters were taken on (the GEMM and its copy helper): any other source reports null.
 FFN_TRAFFIC_BYTES = {
-    "23d3c310a0ec016629cdb9c251d67b08d14b3f19f816719505763ac2b0edbf9c": 2_027_439_378,
+    "ddc4782f1eda1a6b880ca5ee561e64fc49c98a5c7fbdb1b2be2723979072e6cf": 2_204_306_450,
 }
-FFN_SOURCES = ("ffn.hip", "lds_dma.h")
+FFN_SOURCES = ("gemm256.hip", "lds_dma.h")
 
 
 def ffn_source_hash():
@@ -679,7 +679,7 @@ def main():
                    "requests": cfg.requests, "hidden": cfg.hidden, "inter": cfg.inter,
                    "n_pub": cfg.n_pub, "n_priv": cfg.n_priv, "top_k": cfg.top_k,
                    "policy": "4 allow + 4 deny requests", "router": "fp32", "experts": "bf16"},
-        "roofline": {"kernel": "pmpe_expert_ffn (gemm_bf16_kernel GEMM1 + GEMM2)",
+        "roofline": {"kernel": "pmpe_expert_ffn (gemm256_kernel GEMM1 + GEMM2)",
                      "bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS,
                      "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS,
                      "traffic": FFN_TRAFFIC_BYTES.get(ffn_source_hash()),
