@@ -167,6 +167,101 @@ __global__ __launch_bounds__(64) void sha256_chunks_kernel(const uint8_t* __rest
                __builtin_bswap32(s[7])};
 }
 
+// Inner tree levels: node c hashes the digests [c*512, min((c+1)*512, nbytes)) of the level below
+// (nbytes a multiple of 32) into out[32c, 32c+32). There are too few nodes to hide a thread's
+// chain of nine compressions, so two waves share it: wave 0 loads the message, expands block b + 1
+// into its 64 schedule words (round constants added) in LDS while wave 1 runs the 64 rounds of
+// block b: 26 -> 19.5 us for a level of up to 4,608 nodes. Once every CU has several blocks the
+// expanding waves compete with the others (73,728 nodes: 50 -> 54 us), so larger levels keep a
+// thread per node.
+constexpr int kNodes = 64;  // nodes per block, one per lane
+constexpr uint64_t kMaxSplitNodes = 2 * 256 * kNodes;  // two blocks per CU
+__global__ __launch_bounds__(128) void sha256_nodes_kernel(const uint8_t* __restrict__ src, uint64_t nbytes,
+                                                           uint64_t nnodes, uint8_t* __restrict__ out) {
+  __shared__ u32x4 s_kw[2][16][kNodes];
+  constexpr uint32_t kChunk = kFpFanout * 32;
+  const int lane = threadIdx.x & 63;
+  const bool expand = threadIdx.x < 64;  // wave 0
+  const uint64_t c0 = (uint64_t)blockIdx.x * kNodes, c = c0 + lane;
+  auto length = [&](uint64_t node) {
+    const uint64_t off = node * kChunk;
+    return off >= nbytes ? 0u : (uint32_t)(nbytes - off < kChunk ? nbytes - off : kChunk);
+  };
+  const uint32_t len = length(c);           // 0 past the last node: hashed, never stored
+  const int nblk = (int)(length(c0) >> 6) + 1;  // the block's first node has the most blocks
+  const int mine = (int)(len >> 6) + 1;         // with the padding (len mod 64 is 0 or 32)
+  const uint8_t* p = src + c * kChunk;
+  u32x4 v[4];
+  auto load = [&](int b) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      v[q] = (uint32_t)(b * 64 + q * 16) < len ? *reinterpret_cast<const u32x4*>(p + b * 64 + q * 16) : u32x4{0, 0, 0, 0};
+  };
+  uint32_t st[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) st[i] = kInit[i];
+  if (expand) load(0);
+  for (int b = 0; b < nblk; ++b) {
+    if (expand) {
+      uint32_t w[16];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[4 * q + j] = __builtin_bswap32(v[q][j]);
+      if (b + 1 < nblk) load(b + 1);
+      if (b == mine - 1) {  // padding: 0x80 after the last byte, the length in bits at the end
+        if (len & 32u) w[8] = 0x80000000u; else w[0] = 0x80000000u;
+        w[15] = len * 8;
+      }
+#pragma unroll
+      for (int t4 = 0; t4 < 16; ++t4) {
+        u32x4 kw;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int t = 4 * t4 + j;
+          if (t >= 16) {
+            const uint32_t w15 = w[(t - 15) & 15], w2 = w[(t - 2) & 15];
+            const uint32_t s0 = xor3(rotr(w15, 7), rotr(w15, 18), w15 >> 3);
+            const uint32_t s1 = xor3(rotr(w2, 17), rotr(w2, 19), w2 >> 10);
+            w[t & 15] = w[t & 15] + s0 + w[(t - 7) & 15] + s1;
+          }
+          kw[j] = w[t & 15] + kRound[t];
+        }
+        s_kw[b & 1][t4][lane] = kw;
+      }
+    }
+    __syncthreads();  // block b's words are there; the other buffer's rounds (b - 1) are done
+    if (!expand) {
+      uint32_t a = st[0], bb = st[1], cc = st[2], d = st[3], e = st[4], f = st[5], g = st[6], h = st[7];
+#pragma unroll
+      for (int t4 = 0; t4 < 16; ++t4) {
+        const u32x4 kw = s_kw[b & 1][t4][lane];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const uint32_t t1 = h + xor3(rotr(e, 6), rotr(e, 11), rotr(e, 25)) + choose(e, f, g) + kw[j];
+          const uint32_t t2 = xor3(rotr(a, 2), rotr(a, 13), rotr(a, 22)) + majority(a, bb, cc);
+          h = g;
+          g = f;
+          f = e;
+          e = d + t1;
+          d = cc;
+          cc = bb;
+          bb = a;
+          a = t1 + t2;
+        }
+      }
+      if (b < mine) {
+        st[0] += a; st[1] += bb; st[2] += cc; st[3] += d;
+        st[4] += e; st[5] += f; st[6] += g; st[7] += h;
+      }
+    }
+  }
+  if (expand || c >= nnodes) return;
+  u32x4* o = reinterpret_cast<u32x4*>(out + 32 * c);
+  o[0] = u32x4{__builtin_bswap32(st[0]), __builtin_bswap32(st[1]), __builtin_bswap32(st[2]), __builtin_bswap32(st[3])};
+  o[1] = u32x4{__builtin_bswap32(st[4]), __builtin_bswap32(st[5]), __builtin_bswap32(st[6]), __builtin_bswap32(st[7])};
+}
+
 hipError_t launch_level(const uint8_t* src, uint64_t nbytes, uint32_t chunk, uint64_t nchunks,
                         uint8_t* out, bool aligned, hipStream_t stream) {
   const dim3 grid((unsigned)((nchunks + 63) / 64));
@@ -193,8 +288,13 @@ hipError_t launch_fingerprint(const FingerprintArgs& a, hipStream_t stream) {
                               n == 1 ? a.digest : buf[cur], aligned, stream);
   while (e == hipSuccess && n > 1) {
     const uint64_t m = (n + kFpFanout - 1) / kFpFanout;
-    e = launch_level(buf[cur], n * 32, kFpFanout * 32, m, m == 1 ? a.digest : buf[cur ^ 1], true,
-                     stream);
+    uint8_t* out = m == 1 ? a.digest : buf[cur ^ 1];
+    if (m <= kMaxSplitNodes) {
+      sha256_nodes_kernel<<<dim3((unsigned)((m + kNodes - 1) / kNodes)), 128, 0, stream>>>(buf[cur], n * 32, m, out);
+      e = hipGetLastError();
+    } else {
+      e = launch_level(buf[cur], n * 32, kFpFanout * 32, m, out, true, stream);
+    }
     cur ^= 1;
     n = m;
   }
