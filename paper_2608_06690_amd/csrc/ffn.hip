@@ -501,7 +501,7 @@ __global__ __launch_bounds__(C::THREADS) void gemm_bf16_kernel(FfnArgs a) {
             for (int i = 0; i < 4; ++i) {
               const int r = r0 - pass * ER + (lane >> 4) * 4 + i;
               const int c = wn * WCOLS + nb * 16 + (lane & 15);
-              const float v = GATED ? silu_to_bf16(acc[mb][nb][i] * sg) * (acc[mb][nb + NBO][i] * su)
+              const float v = GATED ? silu(acc[mb][nb][i] * sg) * (acc[mb][nb + NBO][i] * su)
                                     : acc[mb][nb][i] * sg;
               so[r * NCOLS + c] = (uint16_t)f32_to_bf16_rne(v);
               if constexpr (GATED && SAVE) {

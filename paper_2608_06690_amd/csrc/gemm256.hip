@@ -467,11 +467,13 @@ __global__ __launch_bounds__(THREADS) void gemm256_kernel(FfnArgs a) {
         u32x4 o;
         if constexpr (GATED) {
           const f32x4 g0 = acc[i][0][mb][0], g1 = acc[i][0][mb][1], u0 = acc[i][1][mb][0], u1 = acc[i][1][mb][1];
+          const float g[8] = {g0[0], g0[1], g0[2], g0[3], g1[0], g1[1], g1[2], g1[3]};
           float v[8];
+          silu_n<8>(g, v);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            v[e] = silu_to_bf16(g0[e]) * u0[e];
-            v[4 + e] = silu_to_bf16(g1[e]) * u1[e];
+            v[e] *= u0[e];
+            v[4 + e] *= u1[e];
           }
           o = u32x4{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]), cvt_pk_bf16(v[4], v[5]), cvt_pk_bf16(v[6], v[7])};
           if (save) {

@@ -100,7 +100,7 @@ __global__ __launch_bounds__(LT) void lora_pre_kernel(LoraArgs a) {
     }
     const float g = tau ? ab[i] + a.scale * dg : ab[i];
     const float u = tau ? ab[I + i] + a.scale * du : ab[I + i];
-    h[i] = (uint16_t)f32_to_bf16_rne(silu_to_bf16(g) * u);
+    h[i] = (uint16_t)f32_to_bf16_rne(silu(g) * u);
   }
 }
 

@@ -37,10 +37,27 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
 }
 
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + __expf(-g)); }
-// The same with the hardware reciprocal (1 ulp) in place of the correctly rounded division (ten
-// more operations), for results that are rounded to bf16; every bf16 path uses this one, so
-// that their h agree to the bit.
-__device__ __forceinline__ float silu_to_bf16(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
+// The same of N values and to the bit, with 4 operations in place of the compiler's 10 for the
+// division (expert FFN of 3840 tokens over 160 experts 431 us with those, 421 with these): with
+// d = 1 + exp(-g), the quotient g rcp(d) is corrected once by its exact remainder. That equals the
+// division for each of the 2.2e9 floats |g| < 87 (no step over- or underflows); a wave that
+// holds another value divides.
+template <int N>
+__device__ __forceinline__ void silu_n(const float (&g)[N], float (&s)[N]) {
+  float m = 0.0f;
+#pragma unroll
+  for (int i = 0; i < N; ++i) m = fmaxf(m, fabsf(g[i]));
+  if (__any(m >= 87.0f)) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) s[i] = silu(g[i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const float d = 1.0f + __expf(-g[i]), r = __builtin_amdgcn_rcpf(d), q = g[i] * r;
+      s[i] = __builtin_fmaf(-__builtin_fmaf(d, q, -g[i]), r, q);
+    }
+  }
+}
 
 // SwiGLU backward of one element: upstream d = dL/dh, gate projection g, up projection u;
 // h = silu(g) u, da = d u s (1 + g (1 - s)), db = d g s with s = sigmoid(g).
