@@ -908,19 +908,27 @@ void launch_f32(const FfnArgs& a, hipStream_t s, int parts) {
 }  // namespace
 
 namespace {
-// Which bf16 grouped products (N = a.H output columns of the last one) run on the 256 x 256
-// kernel: by the average rows per routed expert, as the host does not know the counts. Its
-// tiles read a weight once per 256 rows where the 64-row tiles read it once per 64, so they win
-// as soon as many experts exceed 64 rows (Qwen3-30B-A3B-shaped expert FFN, us with 64-row /
-// 256-row tiles: 512 tokens 313 / 320, 768 331 / 331, 1536 421 / 377, 2048 563 / 409, 2500 639
-// / 402; all in the public pool 512 215 / 250, 1111 400 / 285; DeepSeek-V2-Lite-shaped 400
-// 305 / 312, 800 462 / 370, 1600 744 / 445): from 48 rows on. With fewer than two such tiles
-// per CU the larger tiles leave CUs idle and the line lies at 112 rows (52 experts of 1664 x
-// 640: 1111 tokens, 85 rows, 105 / 136; 1536 tokens, 118 rows, 158 / 137).
+// 256 x 256 tiles that the GEMM2 has at least (N = a.H; one M tile per routed expert), per CU of the
+// card's 256: with few of them the last round of tiles leaves a large share of the CUs idle.
+bool tiles_per_cu(const FfnArgs& a, int n) {
+  return (int64_t)(a.n_pub + a.n_priv) * ((a.H + 255) / 256) >= (int64_t)n * 256;
+}
+
+// Which bf16 grouped products run on the 256 x 256 kernel: by the average rows per routed expert,
+// as the host does not know the counts. Its tiles read a weight once per 256 rows where the 64-row
+// tiles read it once per 64, so they win where many experts have more than 64 rows; below, the
+// 64-row tiles with two blocks per CU stream the weights faster. Measured, expert FFN in us with
+// 64-row / 256-row tiles, rows drawn per expert (evenly) or for two pools of unequal load:
+//   4 and more tiles per CU (160 experts of 2048 x 768), evenly 48 rows 310 / 343, 56 341 / 350,
+//   64 417 / 351; half the tokens private 48 330 / 332, 56 360 / 348; none private 48 310 / 299, 52
+//   355 / 268: from 52 rows on;
+//   2 to 4 (32 experts of 4096 x 1536), evenly 48 212 / 256, 64 308 / 261; unequal 56 262 / 293, 64
+//   292 / 295: from 64 on;
+//   fewer (48 experts of 1152 x 704), evenly 112 99 / 101, 120 100 / 116, 128 116 / 116, 160 123 /
+//   117 (52 experts of 1664 x 640: 120 123 / 131, 128 138 / 133): from 128 on.
 bool use_gemm256(const FfnArgs& a) {
   const int64_t rows = (int64_t)a.T * a.k, E = a.n_pub + a.n_priv;
-  const bool few_tiles = E * ((a.H + 255) / 256) < 512;
-  return rows >= (few_tiles ? 112 : 48) * E;
+  return rows >= (tiles_per_cu(a, 4) ? 52 : tiles_per_cu(a, 2) ? 64 : 128) * E;
 }
 }  // namespace
 

@@ -86,9 +86,12 @@ def test_tile_edges(counts, hidden, inter, form):
     assert int(status) == 0
 
 
-@pytest.mark.parametrize("tokens", [48 * 64 - 1, 48 * 64])  # last batch of the 64-row tiles, first of the 256-row ones
-def test_both_sides_of_the_tile_choice(tokens):
-    n, hidden, inter = 32, 2048, 64
+# the last batch of the 64-row tiles and the first of the 256-row ones, for hidden sizes that make at
+# least four, two and less than two 256 x 256 tiles per CU with 64 experts
+@pytest.mark.parametrize("hidden,tokens", [(4096, 52 * 64 - 1), (4096, 52 * 64), (2048, 64 * 64 - 1), (2048, 64 * 64),
+                                           (1024, 128 * 64 - 1), (1024, 128 * 64)])
+def test_both_sides_of_the_tile_choice(hidden, tokens):
+    n, inter = 32, 64
     d = P.make_desc(hidden, inter, n, n, 1)
     g = torch.Generator(device="cuda").manual_seed(tokens)
     x = torch.empty(tokens, hidden, dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
