@@ -942,10 +942,13 @@ hipError_t launch_expert_ffn_fp8(const FfnArgs& a, hipStream_t s) {
     int v = 0;
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) ncu = v;
   }
-  // The 64-row tiles with two blocks per CU win up to several hundred rows per expert
-  // (Qwen3-30B-A3B-shaped layer pass, us with 64-row / 256-row tiles: 1111 tokens 282 / 362,
-  // 2600 395 / 445, 4096 545 / 554, 8192 954 / 968, 16384 1,749 / 1,666).
-  const bool large = (int64_t)a.T * a.k >= (int64_t)768 * E;
+  // The 64-row tiles with two blocks per CU win up to several hundred rows per expert; expert FFN in
+  // us with 256-row / 64-row tiles: fewer than two 256 x 256 tiles per CU (52 experts of 1664 x 640, half
+  // the tokens private) 128 rows 138 / 83, 384 249 / 187, 640 305 / 291, (48 of 1152 x 704, evenly) 768
+  // 323 / 322: up to 768 rows. With more tiles the large ones fill the chip earlier (160 experts of
+  // 2048 x 768, half the tokens private) 192 rows 466 / 454, 320 666 / 682, 384 748 / 797, 704 1,281 /
+  // 1,377: up to 384.
+  const bool large = (int64_t)a.T * a.k >= (int64_t)(tiles_per_cu(a, 2) ? 384 : 768) * E;
   auto run = [&](auto cfg) {
     using C = decltype(cfg);
     auto grid = [&](int ncols, bool gemm1) {

@@ -9,6 +9,7 @@ import pytest
 import torch
 
 import paper_2608_06690_amd as P
+from paper_2608_06690_amd import _native as N
 import workloads as W
 from oracle import pmpe_oracle as O
 from tests import pmpe_cases as C
@@ -36,12 +37,18 @@ def fp8_layer(cfg, device="cuda"):
     return layer, Lw, fp8
 
 
+# 256-row tiles from 768 rows per expert on, or 384 with at least 512 tiles of 256 x 256 (64 experts of
+# hidden size 2048): the last batch below each line, the first at it and ragged ones above it
+FEW = dict(requests=8, hidden=256, inter=256, n_pub=16, n_priv=8, top_k=4)
+MANY = dict(requests=8, hidden=2048, inter=128, n_pub=48, n_priv=16, top_k=4)
 CASES = [("qwen", dict(tokens=512, requests=4, hidden=256, inter=128, n_pub=16, n_priv=8, top_k=4)),
-         ("qwen", dict(tokens=4096, requests=8, hidden=256, inter=256, n_pub=16, n_priv=8, top_k=4)),
-         ("qwen", {}), ("decode", {})]
+         ("qwen", dict(FEW, tokens=768 * 24 // 4 - 1)), ("qwen", dict(FEW, tokens=768 * 24 // 4)),
+         ("qwen", dict(FEW, tokens=5555)), ("qwen", dict(MANY, tokens=384 * 64 // 4 - 1)),
+         ("qwen", dict(MANY, tokens=384 * 64 // 4)), ("qwen", {}), ("decode", {})]
 
 
-@pytest.mark.parametrize("name,shape", CASES, ids=["small-tiles", "large-tiles", "qwen", "decode"])
+@pytest.mark.parametrize("name,shape", CASES, ids=["small-tiles", "few-below", "few-at", "large-tiles", "many-below",
+                                                   "many-at", "qwen", "decode"])
 def test_fp8_weights_equal_bf16_on_dequantised_weights(name, shape):
     cfg = W.scaled_config(W.get_config(name), **shape) if shape else W.get_config(name)
     log(f"fp8 weights {name} {shape}")
@@ -85,8 +92,9 @@ def test_fp8_layer_matches_oracle():
     del n
 
 
-def test_fp8_all_deny_with_null_private_weights():
-    cfg = W.scaled_config(W.get_config("qwen"), tokens=512, requests=4, hidden=256, inter=128,
+@pytest.mark.parametrize("tokens", [512, 5555])  # 64-row tiles, 256-row tiles
+def test_fp8_all_deny_with_null_private_weights(tokens):
+    cfg = W.scaled_config(W.get_config("qwen"), tokens=tokens, requests=4, hidden=256, inter=128,
                           n_pub=16, n_priv=8, top_k=4)
     layer, Lw, fp8 = fp8_layer(cfg)
     T = cfg.tokens
@@ -101,3 +109,25 @@ def test_fp8_all_deny_with_null_private_weights():
     torch.cuda.synchronize()
     assert torch.equal(out1, b2.out)
     assert int(a2.total.item()) == 0 and int(b2.dev_status.item()) == 0
+
+
+@pytest.mark.parametrize("tokens", [512, 5555])  # 64-row tiles, 256-row tiles
+def test_fp8_private_rows_without_private_weights(tokens):
+    """Allowed tokens whose private weights are missing: their rows are zeroed and not audited, the
+    status bit is set, and the public rows are computed as ever."""
+    cfg = W.scaled_config(W.get_config("qwen"), tokens=tokens, requests=4, hidden=256, inter=128,
+                          n_pub=16, n_priv=8, top_k=4)
+    layer, Lw, fp8 = fp8_layer(cfg)
+    x = W.make_x(cfg, "cuda")
+    words = torch.where(torch.arange(tokens, device="cuda") % 3 == 0,
+                        torch.tensor(P.PMPE_POLICY_ALLOW - 2**32, device="cuda"), 0).to(torch.int32)
+    offs = torch.tensor([0, tokens], device="cuda", dtype=torch.int32)
+    out1 = layer.forward_fp8(x, words, fp8, layer.audit_buffers(tokens, 1), offs).out.clone()
+    a2 = layer.audit_buffers(tokens, 1)
+    b2 = layer.forward_fp8(x, words, fp8[:2] + (None, None) + fp8[4:6] + (None, None), a2, offs)
+    torch.cuda.synchronize()
+    priv = words != 0
+    assert torch.equal(out1[~priv], b2.out[~priv])
+    assert not bool(b2.out[priv].any())
+    assert int(a2.total.item()) == 0 and int(a2.token_rows.sum()) == 0
+    assert int(b2.dev_status.item()) == N.PMPE_DEV_PRIV_WEIGHTS_MISSING
