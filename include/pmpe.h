@@ -302,9 +302,9 @@ pmpe_status pmpe_audit(const pmpe_layer_desc* d, int32_t T, const uint32_t* audi
 
 /*
  * pmpe_layer_forward - the five calls of one layer forward in order (route, dispatch,
- * expert FFN, combine, audit), from one argument block: the same checks, kernels and
- * results as the calls one by one, for callers whose batches are so small that the
- * cost of making five calls shows (decode).
+ * expert FFN, combine, audit), from one argument block, for callers whose batches are so
+ * small that the cost of making five calls shows (decode): the same checks and results as
+ * the calls one by one; the audit reduce may share the combine's launch.
  *
  * Fields are named as in those calls. ffn selects the expert FFN call (PMPE_FFN_*; with
  * PMPE_FFN_FP8 that call gets the descriptor with w_dtype = PMPE_FP8_E4M3, the others `d`

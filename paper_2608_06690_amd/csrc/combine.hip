@@ -6,9 +6,9 @@
 // output bitwise deterministic (no atomics). Slots with token_row = -1 (an invalid
 // expert id upstream) contribute nothing.
 //
-// In a layer forward an extra first block runs the audit reduce (aud.total != NULL): it needs
-// only the expert FFN's counters, so it finishes beside the combine instead of after it
-// (3 to 11 us of a launch of its own).
+// In a layer forward an extra first block may run the audit reduce: it needs only the expert
+// FFN's counters, so it finishes beside the combine instead of after it (3 to 11 us of a launch of
+// its own). The caller decides where that pays.
 #include "audit_block.h"
 
 namespace pmpe {
@@ -19,13 +19,14 @@ constexpr int CB_THREADS = 256;
 // KC > 0: top-k fixed at compile time, so the k row loads of a token are issued
 // together (rows and gates first, then every slot's 16-byte vector) before the sum;
 // KC == 0: any k, one slot at a time. Both add the slots in the same order.
-template <int KC>
-__global__ __launch_bounds__(CB_THREADS) void combine_bf16_kernel(CombineArgs a, AuditArgs aud) {
-  if (aud.total && blockIdx.x == 0) {
+// AUDIT: block 0 reduces the audit, block t + 1 combines token t.
+template <int KC, bool AUDIT>
+__device__ __forceinline__ void combine_bf16(const CombineArgs& a, const AuditArgs& aud) {
+  if (AUDIT && blockIdx.x == 0) {
     audit_block<CB_THREADS / 64>(aud);
     return;
   }
-  const int t = aud.total ? blockIdx.x - 1 : blockIdx.x;
+  const int t = AUDIT ? blockIdx.x - 1 : blockIdx.x;
   const int H = a.H;
   const uint16_t* yp = (const uint16_t*)a.y_perm;
   const uint16_t* ysh = (const uint16_t*)a.y_shared;
@@ -83,12 +84,13 @@ __global__ __launch_bounds__(CB_THREADS) void combine_bf16_kernel(CombineArgs a,
   }
 }
 
-__global__ __launch_bounds__(CB_THREADS) void combine_f32_kernel(CombineArgs a, AuditArgs aud) {
-  if (aud.total && blockIdx.x == 0) {
+template <bool AUDIT>
+__device__ __forceinline__ void combine_f32(const CombineArgs& a, const AuditArgs& aud) {
+  if (AUDIT && blockIdx.x == 0) {
     audit_block<CB_THREADS / 64>(aud);
     return;
   }
-  const int t = aud.total ? blockIdx.x - 1 : blockIdx.x;
+  const int t = AUDIT ? blockIdx.x - 1 : blockIdx.x;
   const int H = a.H;
   const float* yp = (const float*)a.y_perm;
   const float* ysh = (const float*)a.y_shared;
@@ -116,20 +118,37 @@ __global__ __launch_bounds__(CB_THREADS) void combine_f32_kernel(CombineArgs a, 
   }
 }
 
+// (a combine without the audit carries none of it: with the choice at run time it took up to 6 %
+// more at narrow rows)
+template <int KC>
+__global__ __launch_bounds__(CB_THREADS) void combine_bf16_kernel(CombineArgs a) { combine_bf16<KC, false>(a, AuditArgs{}); }
+template <int KC>
+__global__ __launch_bounds__(CB_THREADS) void combine_bf16_audit_kernel(CombineArgs a, AuditArgs aud) { combine_bf16<KC, true>(a, aud); }
+__global__ __launch_bounds__(CB_THREADS) void combine_f32_kernel(CombineArgs a) { combine_f32<false>(a, AuditArgs{}); }
+__global__ __launch_bounds__(CB_THREADS) void combine_f32_audit_kernel(CombineArgs a, AuditArgs aud) { combine_f32<true>(a, aud); }
+
+template <int KC>
+void launch_bf16(const CombineArgs& a, hipStream_t s, const AuditArgs* audit) {
+  if (audit)
+    hipLaunchKernelGGL(combine_bf16_audit_kernel<KC>, dim3((unsigned)a.T + 1), dim3(CB_THREADS), 0, s, a, *audit);
+  else
+    hipLaunchKernelGGL(combine_bf16_kernel<KC>, dim3(a.T), dim3(CB_THREADS), 0, s, a);
+}
+
 }  // namespace
 
 hipError_t launch_combine(const CombineArgs& a, hipStream_t s, const AuditArgs* audit) {
-  const AuditArgs au = audit ? *audit : AuditArgs{};
-  const dim3 grid((unsigned)a.T + (audit ? 1 : 0));
   if (a.act_bf16) {
     switch (a.k) {
-      case 2: hipLaunchKernelGGL(combine_bf16_kernel<2>, grid, dim3(CB_THREADS), 0, s, a, au); break;
-      case 6: hipLaunchKernelGGL(combine_bf16_kernel<6>, grid, dim3(CB_THREADS), 0, s, a, au); break;
-      case 8: hipLaunchKernelGGL(combine_bf16_kernel<8>, grid, dim3(CB_THREADS), 0, s, a, au); break;
-      default: hipLaunchKernelGGL(combine_bf16_kernel<0>, grid, dim3(CB_THREADS), 0, s, a, au); break;
+      case 2: launch_bf16<2>(a, s, audit); break;
+      case 6: launch_bf16<6>(a, s, audit); break;
+      case 8: launch_bf16<8>(a, s, audit); break;
+      default: launch_bf16<0>(a, s, audit); break;
     }
+  } else if (audit) {
+    hipLaunchKernelGGL(combine_f32_audit_kernel, dim3((unsigned)a.T + 1), dim3(CB_THREADS), 0, s, a, *audit);
   } else {
-    hipLaunchKernelGGL(combine_f32_kernel, grid, dim3(CB_THREADS), 0, s, a, au);
+    hipLaunchKernelGGL(combine_f32_kernel, dim3(a.T), dim3(CB_THREADS), 0, s, a);
   }
   return hipGetLastError();
 }

@@ -518,11 +518,19 @@ pmpe_status pmpe_layer_forward(const pmpe_layer_desc* d, int32_t T, pmpe_forward
   }
   if (st != PMPE_OK) return st;
   args->failed = 3;
-  // the audit reduce runs beside the combine, in the same launch, unless its arguments fail
+  // The audit reduce runs beside the combine, in the same launch, unless its arguments fail or
+  // its block (a quarter of the waves of a launch of its own, beside a kernel that keeps the
+  // memory busy) could end after the combine: batches of up to 2048 tokens, and longer ones of few
+  // requests and wide rows, whose combine takes longer. Us of a layer forward with the audit inside
+  // / after: 1000 tokens in 100 requests (hidden 512, top-2) 37 / 39, 4096 in 8 (2048, top-8) 145 /
+  // 149, 16384 in 32 (the same) 482 / 496; but 65536 in 64 (512, top-2) 243 / 224, 4096 in 2000
+  // (2048, top-8) 159 / 154.
   const AuditArgs au{T, a.R, a.audit_token_rows, a.allow, a.req_offset, a.req_private_rows, a.total_private_rows,
                      a.deny_violations};
   const pmpe_status st_audit = a.req_offset ? check_audit(d, au) : PMPE_OK;
-  const bool fused = a.req_offset && st_audit == PMPE_OK && T > 0;
+  const int64_t combine_bytes = ((int64_t)d->top_k + 1) * d->hidden * elem_bytes(d);  // of a token
+  const bool beside = T <= 2048 ? a.R <= 1024 : (a.R <= 64 && combine_bytes >= 16384);
+  const bool fused = a.req_offset && st_audit == PMPE_OK && T > 0 && beside;
   st = combine_impl(d, T, a.y_perm, a.token_row, a.topk_gate, a.y_shared, a.out, stream, fused ? &au : nullptr);
   if (st != PMPE_OK) return st;
   args->failed = 4;

@@ -51,6 +51,30 @@ def test_one_call_equals_the_steps(kind):
     assert int(got[0][9].sum()) > 0
 
 
+# both sides of the rule that puts the audit into the combine's launch (2048 tokens, 1024 requests, and
+# beyond them 64 requests and 16384 bytes of combine per token), and one long request among short ones
+@pytest.mark.parametrize("tokens,requests,hidden", [(2048, 1024, 128), (2048, 1025, 128), (2049, 64, 2048), (2049, 65, 2048),
+                                                    (2049, 64, 1920), (1500, 900, 128), (3000, 3, 2048)])
+def test_audit_beside_and_after_the_combine(tokens, requests, hidden):
+    cfg = W.scaled_config(W.get_config("qwen"), tokens=tokens, requests=1, hidden=hidden, inter=64, n_pub=4, n_priv=4,
+                          top_k=3)
+    Lw = W.make_layer(cfg, 0, "cuda")
+    x = W.make_x(cfg, "cuda")
+    g = torch.Generator().manual_seed(tokens + requests)
+    words = torch.where(torch.rand(tokens, generator=g) < 0.5, P.PMPE_POLICY_ALLOW - 2**32, 0).to(torch.int32).cuda()
+    off = torch.cat([torch.arange(requests), torch.tensor([tokens])]).to(torch.int32).cuda()  # the last one is long
+    got = []
+    for cls in (P.PolicyMaskedMoE, StepByStep):
+        layer = make(cls, cfg, Lw)
+        audit = layer.audit_buffers(tokens, requests)
+        b = layer.forward(x, words, audit, off)
+        got.append([v.clone() for v in (b.out, audit.token_rows, audit.req_rows, audit.total, audit.violations)])
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    rows = got[0][1].long().cumsum(0)
+    ends = torch.cat([rows.new_zeros(1), rows])[off.long()]
+    assert torch.equal(got[0][2], ends[1:] - ends[:-1]) and int(got[0][3]) == int(rows[-1]) > 0
+
+
 def test_failing_step_is_named():
     cfg = W.scaled_config(W.get_config("qwen"), tokens=16, requests=2, hidden=128, inter=64, n_pub=4, n_priv=4, top_k=2)
     layer = make(P.PolicyMaskedMoE, cfg, W.make_layer(cfg, 0, "cuda"))
