@@ -9,18 +9,62 @@
 
 namespace pmpe {
 
-// G requests of one wave at a time, the loads of their first 64 tokens issued together.
-template <int G>
-__device__ __forceinline__ void audit_requests(const AuditArgs& a, int r0, unsigned long long& wtot,
-                                               unsigned int& wviol) {
+// Tokens [lo, hi) of request r, clamped to [0, T).
+__device__ __forceinline__ void audit_span(const AuditArgs& a, int r, int& lo, int& hi) {
+  lo = min(max(a.req_offset[r], 0), a.T);
+  hi = min(max(a.req_offset[r + 1], lo), a.T);
+}
+
+// One wave: counts and violations of the tokens t0, t0 + 64, ... below hi, U loads of each array
+// in flight (past the end the last token is read again and not counted).
+template <int U>
+__device__ __forceinline__ void audit_tokens(const AuditArgs& a, int t0, int hi, unsigned long long& sum,
+                                             unsigned int& viol) {
+  for (int t = t0; t < hi; t += 64 * U) {
+    uint32_t cnt[U], alw[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const int ti = min(t + i * 64, hi - 1);
+      cnt[i] = a.rows[ti];
+      alw[i] = a.allow[ti];
+    }
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const bool in = t + i * 64 < hi;
+      sum += in ? cnt[i] : 0;
+      viol += (in && alw[i] == 0 && cnt[i] > 0) ? 1u : 0u;
+    }
+  }
+}
+
+// One wave: request r.
+__device__ __forceinline__ void audit_request(const AuditArgs& a, int r, unsigned long long& wtot, unsigned int& wviol) {
+  const int lane = threadIdx.x & 63;
+  int lo, hi;
+  audit_span(a, r, lo, hi);
+  unsigned long long sum = 0;
+  if (hi - lo <= 64)
+    audit_tokens<1>(a, lo + lane, hi, sum, wviol);
+  else if (hi - lo <= 256)
+    audit_tokens<4>(a, lo + lane, hi, sum, wviol);
+  else
+    audit_tokens<8>(a, lo + lane, hi, sum, wviol);
+  wtot += sum;
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+  if (lane == 0) a.req_rows[r] = sum;
+}
+
+// One wave: requests r0 .. r0 + 3 (T > 0, r0 < R), the loads of their first 64 tokens together.
+__device__ __forceinline__ void audit_4_requests(const AuditArgs& a, int r0, unsigned long long& wtot, unsigned int& wviol) {
+  constexpr int G = 4;
   const int lane = threadIdx.x & 63;
   int lo[G], hi[G];
   uint32_t cnt[G], alw[G];
+  unsigned long long sum[G];
 #pragma unroll
   for (int i = 0; i < G; ++i) {
-    const int r = min(r0 + i, a.R - 1);
-    lo[i] = min(max(a.req_offset[r], 0), a.T);
-    hi[i] = min(max(a.req_offset[r + 1], lo[i]), a.T);
+    audit_span(a, min(r0 + i, a.R - 1), lo[i], hi[i]);
+    if (r0 + i >= a.R) hi[i] = lo[i];
   }
 #pragma unroll
   for (int i = 0; i < G; ++i) {
@@ -28,69 +72,79 @@ __device__ __forceinline__ void audit_requests(const AuditArgs& a, int r0, unsig
     cnt[i] = a.rows[t];
     alw[i] = a.allow[t];
   }
-  unsigned long long sum[G];
-  unsigned int viol[G];
 #pragma unroll
   for (int i = 0; i < G; ++i) {
     const bool in = lo[i] + lane < hi[i];
     sum[i] = in ? cnt[i] : 0;
-    viol[i] = (in && alw[i] == 0 && cnt[i] > 0) ? 1u : 0u;
-#pragma unroll 8
-    for (int t = lo[i] + 64 + lane; t < hi[i]; t += 64) {  // unrolled: several loads in flight per lane
-      const uint32_t v = a.rows[t];
-      sum[i] += v;
-      viol[i] += (a.allow[t] == 0 && v > 0) ? 1u : 0u;
-    }
+    wviol += (in && alw[i] == 0 && cnt[i] > 0) ? 1u : 0u;
+    audit_tokens<4>(a, lo[i] + 64 + lane, hi[i], sum[i], wviol);
+    wtot += sum[i];
   }
   for (int off = 32; off > 0; off >>= 1) {
 #pragma unroll
-    for (int i = 0; i < G; ++i) {
-      sum[i] += __shfl_xor(sum[i], off, 64);
-      viol[i] += __shfl_xor(viol[i], off, 64);
-    }
+    for (int i = 0; i < G; ++i) sum[i] += __shfl_xor(sum[i], off, 64);
   }
 #pragma unroll
-  for (int i = 0; i < G; ++i) {
-    if (r0 + i >= a.R) break;  // (the last request again: not counted)
-    if (lane == 0) a.req_rows[r0 + i] = sum[i];
-    wtot += sum[i];
-    wviol += viol[i];
-  }
+  for (int i = 0; i < G; ++i)
+    if (lane == 0 && r0 + i < a.R) a.req_rows[r0 + i] = sum[i];
 }
 
-// Every thread of a workgroup of WAVES waves. Short requests: one lane per request. Else one
-// wave per request, or per four of them when every wave has several.
+// Every thread of a workgroup of WAVES waves. Up to 64 requests of more than four tokens on average
+// are walked by the waves. Else requests of up to 16 tokens are walked by one lane each, all at
+// once, and longer ones (a list in LDS) by the waves, one after the other; with many of those the
+// limit of a lane is 64 tokens. A token of a lane costs about 0.08 us, a request of a wave 0.8 us,
+// both latency; the limit is the one that costs less for the lengths at hand. (A rule on the mean
+// length alone gave a long request among short ones to a lane: 200 requests of one token and
+// one of 500 took 46 us, now 5.)
 template <int WAVES>
 __device__ __forceinline__ void audit_block(const AuditArgs& a) {
+  constexpr int THREADS = 64 * WAVES;
   __shared__ unsigned long long s_tot[WAVES];
   __shared__ unsigned int s_viol[WAVES];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  unsigned long long wtot = 0;
+  __shared__ int s_nlong;
+  __shared__ int s_long[THREADS];  // the waves' requests
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  unsigned long long wtot = 0;  // per lane
   unsigned int wviol = 0;
-  // One lane per request where the requests are short: on average up to 16 tokens with at
-  // least 256 of them, up to 4 with more than 16 (200 requests of one token: 15.1 -> 4.5 us;
-  // 37 requests of 30 tokens stay with the waves, 4.8 us).
-  if (a.T == 0 || a.T <= (int64_t)a.R * (a.R >= 256 ? 16 : a.R > 16 ? 4 : 0)) {
-    for (int r = threadIdx.x; r < a.R; r += 64 * WAVES) {
-      const int lo = min(max(a.req_offset[r], 0), a.T);
-      const int hi = min(max(a.req_offset[r + 1], lo), a.T);
-      unsigned long long sum = 0;
-      for (int t = lo; t < hi; ++t) {
-        const uint32_t v = a.rows[t];
-        sum += v;
-        wviol += (a.allow[t] == 0 && v > 0) ? 1u : 0u;
-      }
-      a.req_rows[r] = sum;
-      wtot += sum;
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-      wtot += __shfl_xor(wtot, off, 64);
-      wviol += __shfl_xor(wviol, off, 64);
-    }
-  } else if (a.R > 2 * WAVES) {
-    for (int r = wave * 4; r < a.R; r += WAVES * 4) audit_requests<4>(a, r, wtot, wviol);
+  if (a.R <= WAVES || (a.R <= 64 && a.T > 4 * a.R)) {
+    if (WAVES < 16 && a.R > 2 * WAVES && a.T <= 128 * a.R)  // many short ones for few waves
+      for (int r = 4 * wave; r < a.R; r += 4 * WAVES) audit_4_requests(a, r, wtot, wviol);
+    else
+      for (int r = wave; r < a.R; r += WAVES) audit_request(a, r, wtot, wviol);
   } else {
-    for (int r = wave; r < a.R; r += WAVES) audit_requests<1>(a, r, wtot, wviol);
+    for (int r0 = 0; r0 < a.R; r0 += THREADS) {
+      const int r = r0 + threadIdx.x;
+      int lo = 0, hi = 0;
+      if (r < a.R) audit_span(a, r, lo, hi);
+      const int len = hi - lo;
+      if (threadIdx.x == 0) s_nlong = 0;
+      int limit = 16;
+      const int n16 = __syncthreads_count(len > 16);  // the same in every thread
+      if (n16 > 0) {
+        if (2 * WAVES + n16 > 7 * WAVES + __syncthreads_count(len > 64)) limit = 64;
+        if (len > limit) s_long[atomicAdd(&s_nlong, 1)] = r;
+      }
+      if (r < a.R && len <= limit) {
+        unsigned long long sum = 0;
+        for (int t = lo; t < hi; ++t) {
+          const uint32_t v = a.rows[t];
+          sum += v;
+          wviol += (a.allow[t] == 0 && v > 0) ? 1u : 0u;
+        }
+        a.req_rows[r] = sum;
+        wtot += sum;
+      }
+      if (n16 > 0) {
+        __syncthreads();
+        const int n = s_nlong;
+        for (int i = wave; i < n; i += WAVES) audit_request(a, __builtin_amdgcn_readfirstlane(s_long[i]), wtot, wviol);
+        __syncthreads();  // the list is free for the next requests
+      }
+    }
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    wtot += __shfl_xor(wtot, off, 64);
+    wviol += __shfl_xor(wviol, off, 64);
   }
   if (lane == 0) {
     s_tot[wave] = wtot;
