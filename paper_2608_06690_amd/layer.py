@@ -4,6 +4,7 @@ allocates torch tensors and passes pointers; all computation happens in libpmpe.
 from __future__ import annotations
 
 import dataclasses
+import operator
 from typing import Optional
 
 import torch
@@ -64,7 +65,12 @@ class AuditBuffers:
         return self
 
 
-_STEPS = frozenset(("route", "dispatch", "expert_ffn", "combine", "audit"))
+_STEPS = ("route", "dispatch", "expert_ffn", "combine", "audit")
+_STEP_SET = frozenset(_STEPS)
+_steps_of = operator.attrgetter(*_STEPS)
+# the library calls that the steps make
+_calls_of = operator.attrgetter("pmpe_route", "pmpe_dispatch", "pmpe_expert_ffn", "pmpe_expert_ffn_train",
+                                "pmpe_expert_ffn_fp8", "pmpe_combine", "pmpe_audit")
 
 
 class PolicyMaskedMoE:
@@ -153,9 +159,10 @@ class PolicyMaskedMoE:
                                device=self.device)
 
     def _plain_steps(self) -> bool:
-        # the steps are this class's own: a subclass or an object that replaces one of them
-        # gets the calls one by one
-        return type(self) is PolicyMaskedMoE and _STEPS.isdisjoint(self.__dict__)
+        # the steps and their library calls are the ones written here: where a subclass, an object,
+        # the class or the binding has one replaced, the calls are made one by one
+        return (type(self) is PolicyMaskedMoE and _STEP_SET.isdisjoint(self.__dict__)
+                and _steps_of(PolicyMaskedMoE) == _OWN_STEPS and _calls_of(N) == _OWN_CALLS)
 
     def _forward(self, x, words, b: LayerBuffers, audit: AuditBuffers, req_offset, stream, ffn: int,
                  fp8=None) -> None:
@@ -316,6 +323,9 @@ class PolicyMaskedMoE:
         if req_offset is not None:
             self.audit(x.shape[0], b, audit, req_offset, stream)
         return b
+
+
+_OWN_STEPS, _OWN_CALLS = _steps_of(PolicyMaskedMoE), _calls_of(N)
 
 
 class PrivateAdamW:

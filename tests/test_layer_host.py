@@ -1,6 +1,8 @@
 """Host-side bookkeeping of the layer object (no GPU): the transposed copies of the
 private expert weights that the backward uses are made once, kept across backward
-calls, and remade after an optimizer step, an in-place torch update or new tensors."""
+calls, and remade after an optimizer step, an in-place torch update or new tensors. A step
+of the layer that was replaced, wherever, is the one that a forward calls."""
+import pytest
 import torch
 
 import paper_2608_06690_amd as P
@@ -53,3 +55,32 @@ def test_private_transposes_made_once_and_after_changes(monkeypatch):
     assert len(calls) == 2 and torch.equal(wt[3], lay.w13_priv.transpose(1, 2))
     # the public copies are never remade
     assert all(c not in calls for c in (lay.w2_pub.data_ptr(), lay.w13_pub.data_ptr()))
+
+
+STEPS = ["route", "dispatch", "expert_ffn", "combine", "audit"]
+CALLS = ["pmpe_route", "pmpe_dispatch", "pmpe_expert_ffn", "pmpe_combine", "pmpe_audit"]
+
+
+@pytest.mark.parametrize("where", ["nowhere", "subclass", "object", "class", "binding"])
+@pytest.mark.parametrize("step", range(5))
+def test_a_replaced_step_is_called(monkeypatch, where, step):
+    seen = []
+    monkeypatch.setattr(Lmod.PolicyMaskedMoE, "buffers", lambda self, T: None)
+    monkeypatch.setattr(Lmod.PolicyMaskedMoE, "_forward", lambda self, *a, **k: seen.append("one call"))
+
+    def step_of(name):
+        return lambda *a, **k: seen.append(name)
+
+    lay = make_layer()
+    if where == "subclass":
+        lay.__class__ = type("Traced", (Lmod.PolicyMaskedMoE,), {n: step_of(n) for n in STEPS})
+    elif where == "object":
+        lay.__dict__.update({n: step_of(n) for n in STEPS})
+    elif where == "class":
+        monkeypatch.setattr(Lmod.PolicyMaskedMoE, STEPS[step], step_of(STEPS[step]))
+    elif where == "binding":
+        monkeypatch.setattr(N, CALLS[step], step_of(CALLS[step]))
+    assert lay._plain_steps() == (where == "nowhere")
+    if where in ("nowhere", "subclass", "object"):
+        lay.forward(torch.zeros(4, 16), None, None, torch.tensor([0, 4]))
+        assert seen == (["one call"] if where == "nowhere" else STEPS)
