@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import paper_2608_06690_amd as P
+from paper_2608_06690_amd import _native as N
 from tests import pmpe_cases as C
 
 pytestmark = pytest.mark.gpu
@@ -14,6 +15,9 @@ COUNTS = [
     [127, 129, 0, 256, 257, 1],       # both sides of a half tile and of a tile, an empty expert
     [128, 385, 64, 511, 2, 130],
     [0, 0, 0, 1537, 0, 3],            # one expert with many M tiles (more than one chunk of them)
+    [159, 160, 161, 191, 192, 193],   # row blocks of a second half that hold valid rows
+    [145, 224, 225, 416, 417, 449],   # the same in a second M tile
+    [63, 64, 65, 319, 320, 321],      # few row blocks in a first half
 ]
 SHAPES = [(128, 64), (384, 192), (1664, 320)]  # (hidden, inter)
 
@@ -25,7 +29,7 @@ def reference(x, rows, w13, w2, width):
     return ab, (h @ w2.float().t()).bfloat16()
 
 
-@pytest.mark.parametrize("counts", COUNTS, ids=["edges", "mixed", "tall"])
+@pytest.mark.parametrize("counts", COUNTS, ids=["edges", "mixed", "tall", "blocks", "second", "short"])
 @pytest.mark.parametrize("hidden,inter", SHAPES)
 @pytest.mark.parametrize("form", ["gather", "permuted", "train", "shared"])
 def test_tile_edges(counts, hidden, inter, form):
@@ -111,3 +115,55 @@ def test_both_sides_of_the_tile_choice(hidden, tokens):
         _, y_ref = reference(x, row_token[sl].long(), w13[e], w2[e], inter)
         assert C.rel_l2(y[sl].cpu().double().numpy(), y_ref.cpu().double().numpy()) <= C.RTOL_ROW_BF16, e
     assert int(audit.sum()) == int(count[n:].sum())
+
+
+# Several tiles per block, in rows of every kind (none, part of one half, one half, both, several M tiles): the
+# copies of a tile are then in flight while the one or two before it still multiply and store. K = 64 makes
+# one step per tile (GEMM2 of 4096 x 64, more than five tiles per block), 128 two (GEMM1 of 128 x 2048). The
+# last shape gives a block more tiles than the 256 whose descriptions it keeps.
+@pytest.mark.parametrize("hidden,inter,n", [(4096, 64, 48), (128, 2048, 48), (128, 65536, 80)])
+def test_many_tiles_per_block(hidden, inter, n):
+    rng = np.random.default_rng(inter)
+    kinds = [lambda: 0, lambda: rng.integers(1, 65), lambda: 128, lambda: rng.integers(129, 193), lambda: 256,
+             lambda: rng.integers(193, 300)]
+    counts = [int(kinds[rng.integers(6)]()) for _ in range(2 * n)]
+    counts[-1] = max(1, 128 * 2 * n - sum(counts[:-1]))  # the 256 x 256 kernel runs
+    T = sum(counts)
+    blocks = 256
+    tiles = sum((c + 255) // 256 for c in counts) * max((inter + 127) // 128, (hidden + 255) // 256)
+    assert tiles > (256 if inter == 65536 else 5) * blocks
+    d = P.make_desc(hidden, inter, n, n, 1)
+    g = torch.Generator(device="cuda").manual_seed(inter)
+    x = torch.empty(T, hidden, dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    w13 = torch.empty(2 * n, 2 * inter, hidden, dtype=torch.bfloat16, device="cuda").normal_(0, hidden ** -0.5, generator=g)
+    w2 = torch.empty(2 * n, hidden, inter, dtype=torch.bfloat16, device="cuda").normal_(0, inter ** -0.5, generator=g)
+    offset = np.concatenate([[0], np.cumsum(counts)])
+    count = torch.tensor(counts, dtype=torch.int32, device="cuda")
+    off = torch.tensor(offset, dtype=torch.int32, device="cuda")
+    row_token = torch.randperm(T, generator=g, device="cuda").to(torch.int32)
+    ws = torch.empty(P.pmpe_workspace_bytes(d, T), dtype=torch.uint8, device="cuda")
+    for priv in (True, False):  # private weights given, and missing
+        y = torch.full((T, hidden), 7.0, dtype=torch.bfloat16, device="cuda")
+        audit = torch.zeros(T, dtype=torch.int32, device="cuda")
+        calls = torch.zeros(n, dtype=torch.int32, device="cuda")
+        status = torch.zeros(1, dtype=torch.int32, device="cuda")
+        P.pmpe_expert_ffn(d, T, None, x, count, off, row_token, w13[:n], w2[:n], w13[n:] if priv else None,
+                          w2[n:] if priv else None, None, None, None, y, audit, calls, status, ws)
+        torch.cuda.synchronize()
+        for e in range(2 * n):
+            if counts[e] == 0:
+                continue
+            sl = slice(offset[e], offset[e + 1])
+            if e >= n and not priv:
+                assert not bool(y[sl].any()), e
+                continue
+            _, y_ref = reference(x, row_token[sl].long(), w13[e], w2[e], inter)
+            # row by row: a single wrong tile may not hide in the norm of the others
+            err = (y[sl].float() - y_ref.float()).norm(dim=1) / y_ref.float().norm(dim=1)
+            assert float(err.max()) <= C.RTOL_ROW_BF16, (e, int(err.argmax()))
+        want = torch.zeros(T, dtype=torch.int32, device="cuda")
+        if priv:
+            want[row_token[offset[n]:].long()] = 1
+        assert torch.equal(audit, want)
+        assert calls.tolist() == [int(c > 0 and priv) for c in counts[n:]]
+        assert int(status) == (0 if priv else N.PMPE_DEV_PRIV_WEIGHTS_MISSING)
