@@ -405,21 +405,25 @@ __global__ __launch_bounds__(BT) void bwd_swiglu_kernel(BwdArgs a, const float* 
   }
 }
 
-// Softmax over the whole permitted pool (POOL_SOFTMAX), one wave per token: from the pool
-// logits z_e = x_t . W_r[e] (+ b_e), recomputed by the forward's router kernel (its partial sums
-// over H added in order), p = softmax(z) and dz_e = p_e ([e selected] dg_e - sum_sel p_i dg_i)
-// for every pool member e, written to dz_pool[t, e - first id of the pool] (z may be dz_pool).
-// A logit per wave with x staged in LDS, as before, read 4 H bytes of router rows per logit:
-// 184 us for 2000 tokens of H 2048 over pools of 64 and 16; the router kernel and this one 28.
-__global__ __launch_bounds__(BT) void bwd_pool_dz_kernel(BwdArgs a, const float* z, int zsplit) {
-  constexpr int NPL = 2 * PMPE_MAX_POOL / 64;  // pool members per lane
-  const int t = blockIdx.x * (BT / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (t >= a.T) return;  // wave-uniform; no block barrier follows
-  // the pool of the token is the one its selection lies in (a masked route never mixes
-  // pools; the soft control ranks the concatenated pool)
+// Softmax over the whole permitted pool (POOL_SOFTMAX), one wave per token t: from its pool logits
+// z_e = x_t . W_r[e] (+ b_e) at zt, given as zsplit partial sums pstride apart that are added in
+// order, p = softmax(z) and dz_e = p_e ([e selected] dg_e - sum_sel p_i dg_i) for every pool
+// member e, written to dz_pool[t, e - first id of the pool] (zt may be that row).
+// The pool of the token is the one its selection lies in (a masked route never mixes pools;
+// the soft control ranks the concatenated pool).
+struct TokenPool {
+  int first, n;  // id of its first expert, experts
+};
+__device__ __forceinline__ TokenPool token_pool(const BwdArgs& a, int t) {
   const bool priv = a.topk_idx[(size_t)t * a.k] >= a.n_pub;
-  const int first = a.soft ? 0 : (priv ? a.n_pub : 0);
-  const int pool = a.soft ? a.n_pub + a.n_priv : (priv ? a.n_priv : a.n_pub);
+  if (a.soft) return {0, a.n_pub + a.n_priv};
+  return {priv ? a.n_pub : 0, priv ? a.n_priv : a.n_pub};
+}
+__device__ __forceinline__ void pool_dz(const BwdArgs& a, int t, const float* zt, int zsplit, size_t pstride) {
+  constexpr int NPL = 2 * PMPE_MAX_POOL / 64;  // pool members per lane
+  const int lane = threadIdx.x & 63;
+  const TokenPool tp = token_pool(a, t);
+  const int first = tp.first, pool = tp.n;
   // slot j = lane: the selected expert's position in the pool and its gate gradient
   int sel = -1;
   float dg = 0.f;
@@ -427,8 +431,6 @@ __global__ __launch_bounds__(BT) void bwd_pool_dz_kernel(BwdArgs a, const float*
     sel = a.topk_idx[(size_t)t * a.k + lane] - first;
     dg = a.dz_row[a.token_row[(size_t)t * a.k + lane]];
   }
-  const float* zt = z + (size_t)t * a.pool_stride;
-  const size_t pstride = (size_t)a.T * a.pool_stride;
   float v[NPL], u[NPL], mx = -INFINITY;
 #pragma unroll
   for (int r = 0; r < NPL; ++r) {
@@ -467,6 +469,34 @@ __global__ __launch_bounds__(BT) void bwd_pool_dz_kernel(BwdArgs a, const float*
 #pragma unroll
   for (int r = 0; r < NPL; ++r)
     if (r * 64 + lane < pool) dzp[r * 64 + lane] = v[r] * (u[r] - sum);
+}
+
+// The logits recomputed by the forward's router kernel (z, which may be dz_pool). A logit per wave
+// instead reads 4 H bytes of router rows per logit: 184 us for 2000 tokens of H 2048 over pools
+// of 64 and 16; the router kernel and this one 28.
+__global__ __launch_bounds__(BT) void bwd_pool_dz_kernel(BwdArgs a, const float* z, int zsplit) {
+  const int t = blockIdx.x * (BT / 64) + (threadIdx.x >> 6);
+  if (t >= a.T) return;  // wave-uniform; no block barrier follows
+  pool_dz(a, t, z + (size_t)t * a.pool_stride, zsplit, (size_t)a.T * a.pool_stride);
+}
+
+// The logits recomputed here, block t, one wave per logit: one launch instead of two.
+__global__ __launch_bounds__(BT) void bwd_pool_dz_small_kernel(BwdArgs a) {
+  __shared__ float s_z[2 * PMPE_MAX_POOL];
+  const int t = blockIdx.x, H = a.H, lane = threadIdx.x & 63;
+  const TokenPool tp = token_pool(a, t);
+  const uint16_t* xt = (const uint16_t*)a.x + (size_t)t * H;
+  for (int i = threadIdx.x >> 6; i < tp.n; i += BT / 64) {
+    const int e = tp.first + i;
+    const float* w = e < a.n_pub ? a.wr_pub + (size_t)e * H : a.wr_priv + (size_t)(e - a.n_pub) * H;
+    float s = 0.f;
+#pragma unroll 8
+    for (int h = lane; h < H; h += 64) s += bf16_to_f32(xt[h]) * w[h];
+    s = wave_sum(s);
+    if (lane == 0) s_z[i] = a.bias ? s + a.bias[e] : s;
+  }
+  __syncthreads();
+  if (threadIdx.x < 64) pool_dz(a, t, s_z, 1, 0);
 }
 
 // dx_t = sum_j dXr[r_j] (slot order) + router term + shared-expert term, eight columns per
@@ -537,10 +567,12 @@ __global__ __launch_bounds__(BT) void bwd_dx_kernel(BwdArgs a) {
 }
 
 // The same with POOL_SOFTMAX gates, whose router term is dense: sum over the token's pool of
-// dz_e W_r[e] in id order. A block takes four tokens, so that the pool's router rows are read
-// once for four (51 -> 32 us for 2000 tokens of H 2048 over pools of 64 and 16).
-constexpr int DXP_T = 4;
-template <bool NT>
+// dz_e W_r[e] in id order. With four tokens to a block the pool's router rows are read once for
+// four (51 -> 32 us for 2000 tokens of H 2048 over pools of 64 and 16). With batches that do not fill
+// the chip a token's chain of loads counts, and a block takes one (us with one / four tokens to a
+// block: H 512, pools of 8, 64 tokens 4.0 / 8.2, 3000 7.8 / 10.1; H 2048, pools of 64 and 16, 256
+// 12.6 / 28.2, 1024 24.2 / 27.9, 1536 34.8 / 30.0; H 1024, pools of 32, 2048 16.4 / 19.8, 3000 22.8 / 21.7).
+template <bool NT, int DXP_T>  // DXP_T: tokens per block
 __global__ __launch_bounds__(BT) void bwd_dx_pool_kernel(BwdArgs a) {
   __shared__ int s_r[DXP_T][PMPE_MAX_TOPK];
   __shared__ __attribute__((aligned(16))) float s_dz[2 * PMPE_MAX_POOL][DXP_T];
@@ -602,7 +634,7 @@ __global__ __launch_bounds__(BT) void bwd_dx_pool_kernel(BwdArgs a) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           if (i0 + i >= n) continue;
-          const f32x4 dz = *(const f32x4*)&s_dz[pos + i0 + i][0];
+          const float (&dz)[DXP_T] = s_dz[pos + i0 + i];
 #pragma unroll
           for (int tt = 0; tt < DXP_T; ++tt) {
             if (who & (1 << tt)) {
@@ -755,21 +787,29 @@ hipError_t launch_backward(const BwdArgs& a, hipStream_t s) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (a.pool_gates) {
-    // the pool logits again, by the forward's router kernel: split over H like the forward's
-    // where the partial arrays fit the row-input-gradient buffer (unused until the last
-    // products), else in one piece, straight into dz_pool
-    RouteArgs r{};
-    r.T = a.T; r.H = H; r.n_pub = a.n_pub; r.n_priv = a.n_priv; r.k = a.k; r.act_bf16 = 1;
-    r.x = a.x; r.wr_pub = a.wr_pub; r.wr_priv = a.wr_priv; r.bias = a.bias;
-    r.zstride = a.pool_stride; r.soft = a.soft; r.pool_idx = a.topk_idx;
-    // (the large-batch kernel copies whole 16-byte chunks of the router rows)
-    r.narrow = (((uintptr_t)a.wr_pub | (uintptr_t)a.wr_priv) & 15) != 0;
-    r.zsplit = r.narrow ? 1 : route_ksplit(a.T, H, a.n_pub, a.n_priv, 1);
-    if ((int64_t)r.zsplit * a.pool_stride > (int64_t)a.k * H) r.zsplit = 1;
-    r.z = r.zsplit > 1 ? a.dXr : a.dz_pool;
-    e = launch_route_logits(r, s);
-    if (e != hipSuccess) return e;
-    bwd_pool_dz_kernel<<<(a.T + BT / 64 - 1) / (BT / 64), BT, 0, s>>>(a, r.z, r.zsplit);
+    // Few logits: recomputed where they are used. Us of the pass with them inside / by the router kernel
+    // first (two launches): 64 tokens of H 512, pools of 8 4.9 / 9, of H 1024 5.5 / 9; H 2048, 1024 tokens
+    // 9.2 / 10, 1536 11.6 / 9; pools of 64 and 16, H 512, 64 tokens 12.8 / 10.
+    const int64_t logit = (int64_t)a.pool_stride * H;  // router elements a token reads
+    if (logit <= 16384 && logit * a.T <= ((int64_t)1 << 24)) {
+      bwd_pool_dz_small_kernel<<<a.T, BT, 0, s>>>(a);
+    } else {
+      // the pool logits again, by the forward's router kernel: split over H like the forward's
+      // where the partial arrays fit the row-input-gradient buffer (unused until the last
+      // products), else in one piece, straight into dz_pool
+      RouteArgs r{};
+      r.T = a.T; r.H = H; r.n_pub = a.n_pub; r.n_priv = a.n_priv; r.k = a.k; r.act_bf16 = 1;
+      r.x = a.x; r.wr_pub = a.wr_pub; r.wr_priv = a.wr_priv; r.bias = a.bias;
+      r.zstride = a.pool_stride; r.soft = a.soft; r.pool_idx = a.topk_idx;
+      // (the large-batch kernel copies whole 16-byte chunks of the router rows)
+      r.narrow = (((uintptr_t)a.wr_pub | (uintptr_t)a.wr_priv) & 15) != 0;
+      r.zsplit = r.narrow ? 1 : route_ksplit(a.T, H, a.n_pub, a.n_priv, 1);
+      if ((int64_t)r.zsplit * a.pool_stride > (int64_t)a.k * H) r.zsplit = 1;
+      r.z = r.zsplit > 1 ? a.dXr : a.dz_pool;
+      e = launch_route_logits(r, s);
+      if (e != hipSuccess) return e;
+      bwd_pool_dz_kernel<<<(a.T + BT / 64 - 1) / (BT / 64), BT, 0, s>>>(a, r.z, r.zsplit);
+    }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -919,11 +959,20 @@ hipError_t launch_backward(const BwdArgs& a, hipStream_t s) {
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  const int dxp = (a.T + DXP_T - 1) / DXP_T;
+  auto dx_pool = [&](auto nt, auto tokens) {
+    constexpr int DXP_T = decltype(tokens)::value;
+    bwd_dx_pool_kernel<decltype(nt)::value, DXP_T><<<(a.T + DXP_T - 1) / DXP_T, BT, 0, s>>>(a);
+  };
+  auto dx_pool_tokens = [&](auto nt) {
+    if (a.T <= 1024 || (int64_t)a.T * H <= ((int64_t)1 << 21))
+      dx_pool(nt, std::integral_constant<int, 1>{});
+    else
+      dx_pool(nt, std::integral_constant<int, 4>{});
+  };
   if (a.pool_gates && a.w2t_pub)
-    bwd_dx_pool_kernel<true><<<dxp, BT, 0, s>>>(a);
+    dx_pool_tokens(std::true_type{});
   else if (a.pool_gates)
-    bwd_dx_pool_kernel<false><<<dxp, BT, 0, s>>>(a);
+    dx_pool_tokens(std::false_type{});
   else if (a.w2t_pub)
     bwd_dx_kernel<true><<<a.T, BT, 0, s>>>(a);
   else

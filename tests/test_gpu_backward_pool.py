@@ -1,6 +1,6 @@
-"""The router part of the pool-softmax backward at its edges: token counts around the four tokens
-of a dx block, private pools around the 16 experts of a router-gradient block, hidden sizes
-that leave part of a block idle, and both router kernels behind the recomputed logits."""
+"""The router part of the pool-softmax backward at its edges: token counts around the one or four
+tokens of a dx block, private pools around the 16 experts of a router-gradient block, hidden sizes
+that leave part of a block idle, and both router kernels behind the recomputed logits, or none."""
 import pytest
 import torch
 
@@ -14,6 +14,10 @@ pytestmark = pytest.mark.gpu
     (1, 128, 5, 4, 2), (7, 384, 20, 16, 3), (66, 640, 16, 17, 2), (130, 256, 70, 33, 4),
     (2049, 256, 24, 8, 2),    # H split, partial logits in the row-gradient buffer
     (2100, 128, 256, 20, 1),  # the partial logits would not fit it: one piece
+    (2049, 256, 70, 8, 2),    # H split by the router kernel (fewer logits are recomputed where they are used)
+    (1024, 2048, 8, 8, 2), (1025, 2048, 8, 8, 2),  # logits inside and one token to a dx block; the router kernel and four
+    (1025, 2176, 7, 6, 2),    # logits inside, four tokens to a block, one in the last
+    (2051, 1152, 16, 8, 2),   # the router kernel, four tokens to a block, three in the last
 ])
 @pytest.mark.parametrize("transposed", [True, False])
 def test_pool_softmax_router_gradients(tokens, hidden, n_pub, n_priv, k, transposed):
