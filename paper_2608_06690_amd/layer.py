@@ -170,13 +170,16 @@ class PolicyMaskedMoE:
         if fp8 is None:
             w = (self.w13_pub, self.w2_pub, self.w13_priv, self.w2_priv, self.w13_sh, self.w2_sh, None, None, None, None)
         else:
+            fp8 = tuple(fp8)
             w = (*fp8[:4], None, None, *fp8[4:])
+        # without requests there is no audit call, and only the counters of `audit` are used
+        reduce = (None,) * 4 if req_offset is None else (req_offset, audit.req_rows, audit.total, audit.violations)
         N.pmpe_layer_forward(
             self.desc, x.shape[0],
             (x, self.wr_pub, self.wr_priv, self.bias, words, b.topk_idx, b.topk_gate, b.allow, b.kgap, b.expert_count,
              b.expert_offset, b.row_token, b.token_row, b.x_perm, *w, b.y_shared, b.y_perm,
              b.ab if ffn == N.PMPE_FFN_TRAIN else None, b.out, audit.token_rows,
-             audit.priv_calls, req_offset, audit.req_rows, audit.total, audit.violations, b.dev_status, b.ws),
+             audit.priv_calls, *reduce, b.dev_status, b.ws),
             0 if req_offset is None else req_offset.numel() - 1, ffn, stream)
 
     def combine(self, x, b: LayerBuffers, stream=None):

@@ -2,6 +2,8 @@
 private expert weights that the backward uses are made once, kept across backward
 calls, and remade after an optimizer step, an in-place torch update or new tensors. A step
 of the layer that was replaced, wherever, is the one that a forward calls."""
+import types
+
 import pytest
 import torch
 
@@ -84,3 +86,31 @@ def test_a_replaced_step_is_called(monkeypatch, where, step):
     if where in ("nowhere", "subclass", "object"):
         lay.forward(torch.zeros(4, 16), None, None, torch.tensor([0, 4]))
         assert seen == (["one call"] if where == "nowhere" else STEPS)
+
+
+@pytest.mark.parametrize("offsets", [None, torch.tensor([0, 4], dtype=torch.int32)])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_arguments_of_the_one_call(monkeypatch, offsets, fp8):
+    """A forward without requests needs the counters of its audit argument only, and any iterable of eight
+    fp8 tensors will do."""
+    got = []
+    monkeypatch.setattr(N, "pmpe_layer_forward", lambda d, T, tensors, R, ffn, stream: got.extend((tensors, R, ffn)))
+    lay = make_layer()
+    b = types.SimpleNamespace(**{f: torch.zeros(1) for f in Lmod.LayerBuffers.__dataclass_fields__})
+    monkeypatch.setattr(Lmod.PolicyMaskedMoE, "buffers", lambda self, T: b)
+    counters = dict(token_rows=torch.zeros(4), priv_calls=torch.zeros(2))
+    reduce = dict(req_rows=torch.zeros(1), total=torch.zeros(1), violations=torch.zeros(1))
+    audit = types.SimpleNamespace(**counters, **({} if offsets is None else reduce))
+    x = torch.zeros(4, 16)
+    if fp8:
+        weights = {i: torch.zeros(1) for i in range(8)}
+        lay.forward_fp8(x, None, weights.values(), audit, offsets)
+    else:
+        lay.forward(x, None, audit, offsets)
+    arg = dict(zip(N.ForwardArgs.POINTERS, got[0]))
+    assert len(got[0]) == len(N.ForwardArgs.POINTERS) and got[1] == (0 if offsets is None else 1)
+    assert arg["req_offset"] is offsets and arg["audit_token_rows"] is counters["token_rows"]
+    for name, field in (("req_private_rows", "req_rows"), ("total_private_rows", "total"), ("deny_violations", "violations")):
+        assert arg[name] is (None if offsets is None else reduce[field])
+    if fp8:
+        assert arg["w13_pub"] is weights[0] and arg["w2s_priv"] is weights[7] and arg["w13_sh"] is None
