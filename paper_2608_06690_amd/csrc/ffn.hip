@@ -159,29 +159,12 @@ __global__ __launch_bounds__(C::THREADS) void gemm_bf16_kernel(FfnArgs a) {
   const int TK = a.T * a.k;
 
   if (tid < 64) {
-    // Tile order, prefill tiles (256 rows): the shared group first (all T tokens; in GEMM2
-    // its K loop over 2 I_s is the longest, so its tiles must not be left for the end),
-    // then the public and the private experts interleaved in proportion to the pool sizes
-    // (public j before private p iff (2j+1) n_priv <= (2p+1) n_pub). Each XCD's slice of
-    // the routed tiles then holds both kinds (the private experts' full tiles carry about
-    // twice the MFMA work of the half-filled public ones), while the tiles of one expert
-    // stay adjacent. Decode-shaped tiles keep the expert order (their two blocks per CU
-    // have no LDS to spare for the permutation).
-    const int sh = (ngroups > E) ? 1 : 0;
-    for (int g = tid; MIX && g < ngroups; g += 64) {
-      int pos;
-      if (g < a.n_pub) {
-        const int num = (2 * g + 1) * a.n_priv;  // private experts before public g
-        pos = sh + g + min(a.n_priv, ((num + a.n_pub - 1) / a.n_pub) / 2);
-      } else if (g < E) {
-        const int p = g - a.n_pub;
-        const int f = (2 * p + 1) * a.n_pub / a.n_priv;  // public experts before private p
-        pos = sh + p + min(a.n_pub, (f + 1) / 2);
-      } else {
-        pos = 0;
-      }
-      s_perm[pos] = g;
-    }
+    // Tile order, prefill tiles (256 rows): the public and the private experts interleaved
+    // (mixed_position). Each XCD's slice of the tiles then holds both kinds (the private
+    // experts' full tiles carry about twice the MFMA work of the half-filled public ones),
+    // while the tiles of one expert stay adjacent. Decode-shaped tiles keep the expert order,
+    // the shared group last (their two blocks per CU have no LDS to spare for the permutation).
+    for (int g = tid; MIX && g < ngroups; g += 64) s_perm[mixed_position(g, a.n_pub, a.n_priv)] = g;
     // (this wave's LDS writes above precede its reads below)
     int running = 0;
     for (int o0 = 0; o0 < ngroups; o0 += 64) {
@@ -204,29 +187,18 @@ __global__ __launch_bounds__(C::THREADS) void gemm_bf16_kernel(FfnArgs a) {
   __syncthreads();
 
   // Block ids are remapped so that XCD x (workgroups go to the 8 XCDs round-robin) takes
-  // one contiguous slice of the routed tiles, dealt round-robin to its blocks: tiles that
-  // share an expert's weights or rows then run on one XCD and meet in its L2. The shared
-  // group's tiles (prefill) come before them in every XCD's list, dealt to the XCDs in
-  // chunks of XCH consecutive tiles (M tiles of one weight tile), so that every XCD gets
-  // its share of them.
-  constexpr int XCH = 8;
+  // one contiguous slice of the tiles, dealt round-robin to its blocks: tiles that share an
+  // expert's weights or rows then run on one XCD and meet in its L2.
   const int total = s_cum[ngroups];
-  const int n_sh = (MIX && ngroups > E) ? s_cum[1] : 0;  // shared tiles, first in the order
-  const int n_rt = total - n_sh;
   const int b = blockIdx.x, x = b & 7, q = b >> 3;
   const int nbx = ((int)gridDim.x - x + 7) >> 3;
-  const int nch = (n_sh + XCH - 1) / XCH;               // chunks of shared tiles
-  const int nch_x = (nch > x) ? (nch - x + 7) / 8 : 0;  // those of XCD x
-  // the last chunk (nch - 1) is the only one that may be partial
-  const int sh_x = nch_x * XCH - ((nch_x > 0 && (nch - 1) % 8 == x) ? (nch * XCH - n_sh) : 0);
-  const int cnt_x = sh_x + (n_rt >> 3) + (x < (n_rt & 7) ? 1 : 0);
-  const int start_x = n_sh + x * (n_rt >> 3) + min(x, n_rt & 7);
+  const int cnt_x = (total >> 3) + (x < (total & 7) ? 1 : 0);
+  const int start_x = x * (total >> 3) + min(x, total & 7);
   const int ntl = (cnt_x > q && q < nbx) ? (cnt_x - q + nbx - 1) / nbx : 0;
   if (ntl == 0) return;
 
   auto tile_of = [&](int i) {
-    const int j = q + i * nbx;  // index within the XCD's tiles
-    const int L = (j < sh_x) ? (x + 8 * (j / XCH)) * XCH + (j % XCH) : start_x + (j - sh_x);
+    const int L = start_x + q + i * nbx;
     int lo = 0, hi = ngroups - 1;  // last position o with s_cum[o] <= L (a group with tiles)
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
@@ -947,7 +919,9 @@ hipError_t launch_expert_ffn_fp8(const FfnArgs& a, hipStream_t s) {
   // the tokens private) 128 rows 138 / 83, 384 249 / 187, 640 305 / 291, (48 of 1152 x 704, evenly) 768
   // 323 / 322: up to 768 rows. With more tiles the large ones fill the chip earlier (160 experts of
   // 2048 x 768, half the tokens private) 192 rows 466 / 454, 320 666 / 682, 384 748 / 797, 704 1,281 /
-  // 1,377: up to 384.
+  // 1,377: up to 384 (drawn evenly 320 rows 20 % less, so the line is not lower). Between the two kinds
+  // the rounds of tiles decide: 16 experts of 7168 x 2048 (1.75 tiles per CU) take 20 % less with the
+  // 64-row tiles at 256 rows, 13 % more at 128 and 448.
   const bool large = (int64_t)a.T * a.k >= (int64_t)(tiles_per_cu(a, 2) ? 384 : 768) * E;
   auto run = [&](auto cfg) {
     using C = decltype(cfg);

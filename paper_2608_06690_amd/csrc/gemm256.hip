@@ -110,24 +110,10 @@ __global__ __launch_bounds__(THREADS) void gemm256_kernel(FfnArgs a) {
   if (tid < 64) {
     // Tile order: the shared group first (all T tokens; in GEMM2 its K loop over 2 I_s is the
     // longest, so its tiles must not be left for the end), then the public and the private
-    // experts interleaved in proportion to the pool sizes (public j before private p iff
-    // (2j+1) n_priv <= (2p+1) n_pub): each XCD's slice then holds full and half-filled tiles
-    // alike, while the tiles of one expert stay adjacent.
+    // experts interleaved (mixed_position): each XCD's slice then holds full and half-filled
+    // tiles alike, while the tiles of one expert stay adjacent.
     const int sh = (ngroups > E) ? 1 : 0;
-    for (int g = tid; g < ngroups; g += 64) {
-      int pos;
-      if (g < a.n_pub) {
-        const int num = (2 * g + 1) * a.n_priv;  // private experts before public g
-        pos = sh + g + min(a.n_priv, ((num + a.n_pub - 1) / a.n_pub) / 2);
-      } else if (g < E) {
-        const int p = g - a.n_pub;
-        const int f = (2 * p + 1) * a.n_pub / a.n_priv;  // public experts before private p
-        pos = sh + p + min(a.n_pub, (f + 1) / 2);
-      } else {
-        pos = 0;
-      }
-      s_perm[pos] = g;
-    }
+    for (int g = tid; g < ngroups; g += 64) s_perm[g < E ? sh + mixed_position(g, a.n_pub, a.n_priv) : 0] = g;
     // (this wave's LDS writes above precede its reads below)
     int running = 0;
     for (int o0 = 0; o0 < ngroups; o0 += 64) {

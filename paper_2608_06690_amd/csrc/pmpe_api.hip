@@ -125,7 +125,7 @@ pmpe_status check_backward_desc(const pmpe_layer_desc* d, int32_t T) {
   // the grouped GEMMs address [T*k, 2I] rows with 32-bit element offsets
   if ((int64_t)T * d->top_k * 2 * d->inter >= ((int64_t)1 << 31)) return PMPE_ERR_SHAPE;
   if (d->n_shared > 0 && ((int64_t)d->n_shared * d->shared_inter) % 128 != 0) return PMPE_ERR_SHAPE;
-  // the pool-softmax pass stages one x row in fp32 LDS
+  // a limit of the interface (pmpe.h); the kernels have none below check_desc's
   if (d->gate_mode == PMPE_GATE_POOL_SOFTMAX && d->hidden > 8192) return PMPE_ERR_SHAPE;
   return PMPE_OK;
 }

@@ -107,6 +107,19 @@ __device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src) {
   return ((uint64_t)hi << 32) | lo;
 }
 
+// Position of expert e in the order of the grouped GEMMs on 256-row tiles: the public and the private
+// experts interleaved in proportion to the pool sizes (public j before private p iff
+// (2j+1) n_priv <= (2p+1) n_pub).
+__device__ __forceinline__ int mixed_position(int e, int n_pub, int n_priv) {
+  if (e < n_pub) {
+    const int num = (2 * e + 1) * n_priv;  // private experts before public e
+    return e + min(n_priv, ((num + n_pub - 1) / n_pub) / 2);
+  }
+  const int p = e - n_pub;
+  const int f = (2 * p + 1) * n_pub / n_priv;  // public experts before private p
+  return p + min(n_pub, (f + 1) / 2);
+}
+
 // ---------------------------------------------------------------------------
 // Launchers (arguments already validated; T > 0)
 // ---------------------------------------------------------------------------
