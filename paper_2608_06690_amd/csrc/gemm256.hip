@@ -34,15 +34,15 @@
 // epilogue goes from the accumulators to 16-byte stores without LDS or barriers.
 //
 // What bounds it: the global->LDS copies. Measured per call of the two forward products (MI355X;
-// timing builds): 16384 tokens over 32 experts 1,202 us, copies alone 913, MFMAs and LDS reads
-// alone 767; 4096 tokens over 160 experts 493, 415 and 317. About 64 lines per CU are on their
-// way from L2 whatever is issued ahead (counters), so a line's latency sets the copy rate, and
-// copies issued in a burst stall the wave that issues them: one copy after every fourth to
-// eighth MFMA of the multiplying wave (1,245 -> 1,189 us) beats the reading wave issuing them.
-// Against one two-stage ring drained at every step (the previous kernel): 16384-token layer
-// 1,466 -> 1,320 us, DeepSeek-V2-Lite-shaped 8192-token layer 1,307 -> 1,230 us,
-// Qwen3-30B-A3B-shaped 4096-token layer 558 -> 522 us (of it the last weight half tile of a
-// step without A1 between the MFMAs: expert FFN 471 -> 464 us).
+// timing builds before the short last halves): 16384 tokens over 32 experts 1,202 us, copies alone
+// 913, MFMAs and LDS reads alone 767; 4096 tokens over 160 experts 493, 415 and 317. 46 to 68
+// lines per CU are on their way from L2 whatever is issued ahead (read latency times requests over
+// the kernel's time, counters of both batches), so a line's latency sets the copy rate, and copies
+// issued in a burst stall the wave that issues them: one copy after every fourth to eighth MFMA of
+// the multiplying wave (1,245 -> 1,189 us) beats the reading wave issuing them. Against one
+// two-stage ring drained at every step (the kernel before it): 16384-token layer 1,466 -> 1,345
+// us (1,315 with a reciprocal in place of silu's division), DeepSeek-V2-Lite-shaped 8192-token
+// layer 1,307 -> 1,240, Qwen3-30B-A3B-shaped 4096-token layer 558 -> 502.
 #include "lds_dma.h"
 #include "pmpe_internal.h"
 
