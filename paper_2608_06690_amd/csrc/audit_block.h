@@ -15,7 +15,7 @@ __device__ __forceinline__ void audit_span(const AuditArgs& a, int r, int& lo, i
   hi = min(max(a.req_offset[r + 1], lo), a.T);
 }
 
-// One wave: counts and violations of the tokens t0, t0 + 64, ... below hi, U loads of each array
+// This lane's share of a wave's walk: the tokens t0, t0 + 64, ... below hi, U loads of each array
 // in flight (past the end the last token is read again and not counted).
 template <int U>
 __device__ __forceinline__ void audit_tokens(const AuditArgs& a, int t0, int hi, unsigned long long& sum,
@@ -37,30 +37,34 @@ __device__ __forceinline__ void audit_tokens(const AuditArgs& a, int t0, int hi,
   }
 }
 
-// One wave: request r.
-__device__ __forceinline__ void audit_request(const AuditArgs& a, int r, unsigned long long& wtot, unsigned int& wviol) {
+// One wave: request r of tokens [lo, hi) (the same in every lane, like what is added to the totals).
+__device__ __forceinline__ void audit_request(const AuditArgs& a, int r, int lo, int hi, unsigned long long& wtot, unsigned int& wviol) {
   const int lane = threadIdx.x & 63;
-  int lo, hi;
-  audit_span(a, r, lo, hi);
   unsigned long long sum = 0;
+  unsigned int viol = 0;
   if (hi - lo <= 64)
-    audit_tokens<1>(a, lo + lane, hi, sum, wviol);
+    audit_tokens<1>(a, lo + lane, hi, sum, viol);
   else if (hi - lo <= 256)
-    audit_tokens<4>(a, lo + lane, hi, sum, wviol);
+    audit_tokens<4>(a, lo + lane, hi, sum, viol);
   else
-    audit_tokens<8>(a, lo + lane, hi, sum, wviol);
-  wtot += sum;
-  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    audit_tokens<8>(a, lo + lane, hi, sum, viol);
+  for (int off = 32; off > 0; off >>= 1) {
+    sum += __shfl_xor(sum, off, 64);
+    viol += __shfl_xor(viol, off, 64);
+  }
   if (lane == 0) a.req_rows[r] = sum;
+  wtot += sum;
+  wviol += viol;
 }
 
-// One wave: requests r0 .. r0 + 3 (T > 0, r0 < R), the loads of their first 64 tokens together.
+// The same for requests r0 .. r0 + 3 (T > 0, r0 < R), the loads of their first 64 tokens together.
 __device__ __forceinline__ void audit_4_requests(const AuditArgs& a, int r0, unsigned long long& wtot, unsigned int& wviol) {
   constexpr int G = 4;
   const int lane = threadIdx.x & 63;
   int lo[G], hi[G];
   uint32_t cnt[G], alw[G];
   unsigned long long sum[G];
+  unsigned int viol = 0;
 #pragma unroll
   for (int i = 0; i < G; ++i) {
     audit_span(a, min(r0 + i, a.R - 1), lo[i], hi[i]);
@@ -76,75 +80,85 @@ __device__ __forceinline__ void audit_4_requests(const AuditArgs& a, int r0, uns
   for (int i = 0; i < G; ++i) {
     const bool in = lo[i] + lane < hi[i];
     sum[i] = in ? cnt[i] : 0;
-    wviol += (in && alw[i] == 0 && cnt[i] > 0) ? 1u : 0u;
-    audit_tokens<4>(a, lo[i] + 64 + lane, hi[i], sum[i], wviol);
-    wtot += sum[i];
+    viol += (in && alw[i] == 0 && cnt[i] > 0) ? 1u : 0u;
+    audit_tokens<4>(a, lo[i] + 64 + lane, hi[i], sum[i], viol);
   }
   for (int off = 32; off > 0; off >>= 1) {
 #pragma unroll
     for (int i = 0; i < G; ++i) sum[i] += __shfl_xor(sum[i], off, 64);
+    viol += __shfl_xor(viol, off, 64);
   }
 #pragma unroll
-  for (int i = 0; i < G; ++i)
+  for (int i = 0; i < G; ++i) {
     if (lane == 0 && r0 + i < a.R) a.req_rows[r0 + i] = sum[i];
+    wtot += sum[i];
+  }
+  wviol += viol;
 }
 
-// Every thread of a workgroup of WAVES waves. Up to 64 requests of more than four tokens on average
-// are walked by the waves. Else requests of up to 16 tokens are walked by one lane each, all at
-// once, and longer ones (a list in LDS) by the waves, one after the other; with many of those the
-// limit of a lane is 64 tokens. A token of a lane costs about 0.08 us, a request of a wave 0.8 us,
-// both latency; the limit is the one that costs less for the lengths at hand. (A rule on the mean
-// length alone gave a long request among short ones to a lane: 200 requests of one token and
-// one of 500 took 46 us, now 5.)
+// Every thread of a workgroup of WAVES waves. Up to 16 requests are walked by a wave each, and more of them
+// where they are long on average (more than 4 tokens for up to 64 requests, 16 for up to 256, 64 for
+// more: lanes in fewer than 16 waves would have the longer ones in one line). Else a wave takes 64 requests at a time: those of up to 16 tokens (64 where it has many
+// of 17 to 64) are walked by one lane each, all at once, and longer ones by the whole wave, one after
+// the other. A token of a lane costs about 0.08 us, a request of a wave up to 0.8 us, both latency.
+// (A rule on the mean length alone gave a long request among short ones to a lane: 200 requests of
+// one token and one of 500 took 46 us, now 4; a list of the long ones for all waves costs every
+// batch two block barriers, 10,000 requests of 1.6 tokens 14 us, now 9.)
 template <int WAVES>
 __device__ __forceinline__ void audit_block(const AuditArgs& a) {
-  constexpr int THREADS = 64 * WAVES;
   __shared__ unsigned long long s_tot[WAVES];
   __shared__ unsigned int s_viol[WAVES];
-  __shared__ int s_nlong;
-  __shared__ int s_long[THREADS];  // the waves' requests
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  unsigned long long wtot = 0;  // per lane
+  unsigned long long wtot = 0;  // of the wave
   unsigned int wviol = 0;
-  if (a.R <= WAVES || (a.R <= 64 && a.T > 4 * a.R)) {
-    if (WAVES < 16 && a.R > 2 * WAVES && a.T <= 128 * a.R)  // many short ones for few waves
+  if (a.R <= 16 || a.T > (int64_t)a.R * (a.R <= 64 ? 4 : a.R <= 256 ? 16 : 64)) {
+    if (WAVES < 16 && a.R > 2 * WAVES && a.T <= 128 * a.R) {  // many short ones for few waves
       for (int r = 4 * wave; r < a.R; r += 4 * WAVES) audit_4_requests(a, r, wtot, wviol);
-    else
-      for (int r = wave; r < a.R; r += WAVES) audit_request(a, r, wtot, wviol);
+    } else {
+      for (int r = wave; r < a.R; r += WAVES) {
+        int lo, hi;
+        audit_span(a, r, lo, hi);
+        audit_request(a, r, lo, hi, wtot, wviol);
+      }
+    }
   } else {
-    for (int r0 = 0; r0 < a.R; r0 += THREADS) {
-      const int r = r0 + threadIdx.x;
+    unsigned long long ltot = 0;  // this lane's requests
+    unsigned int lviol = 0;
+    for (int r0 = wave * 64; r0 < a.R; r0 += 64 * WAVES) {
+      const int r = r0 + lane;
       int lo = 0, hi = 0;
       if (r < a.R) audit_span(a, r, lo, hi);
       const int len = hi - lo;
-      if (threadIdx.x == 0) s_nlong = 0;
       int limit = 16;
-      const int n16 = __syncthreads_count(len > 16);  // the same in every thread
-      if (n16 > 0) {
-        if (2 * WAVES + n16 > 7 * WAVES + __syncthreads_count(len > 64)) limit = 64;
-        if (len > limit) s_long[atomicAdd(&s_nlong, 1)] = r;
+      uint64_t longer = __ballot(len > 16);
+      if (longer != 0) {
+        const uint64_t over64 = __ballot(len > 64);
+        if (__popcll(longer) - __popcll(over64) > 5) {
+          limit = 64;
+          longer = over64;
+        }
       }
       if (r < a.R && len <= limit) {
         unsigned long long sum = 0;
         for (int t = lo; t < hi; ++t) {
           const uint32_t v = a.rows[t];
           sum += v;
-          wviol += (a.allow[t] == 0 && v > 0) ? 1u : 0u;
+          lviol += (a.allow[t] == 0 && v > 0) ? 1u : 0u;
         }
         a.req_rows[r] = sum;
-        wtot += sum;
+        ltot += sum;
       }
-      if (n16 > 0) {
-        __syncthreads();
-        const int n = s_nlong;
-        for (int i = wave; i < n; i += WAVES) audit_request(a, __builtin_amdgcn_readfirstlane(s_long[i]), wtot, wviol);
-        __syncthreads();  // the list is free for the next requests
+      for (; longer != 0; longer &= longer - 1) {
+        const int i = __builtin_ctzll(longer);
+        audit_request(a, r0 + i, __builtin_amdgcn_readlane(lo, i), __builtin_amdgcn_readlane(hi, i), wtot, wviol);
       }
     }
-  }
-  for (int off = 32; off > 0; off >>= 1) {
-    wtot += __shfl_xor(wtot, off, 64);
-    wviol += __shfl_xor(wviol, off, 64);
+    for (int off = 32; off > 0; off >>= 1) {
+      ltot += __shfl_xor(ltot, off, 64);
+      lviol += __shfl_xor(lviol, off, 64);
+    }
+    wtot += ltot;
+    wviol += lviol;
   }
   if (lane == 0) {
     s_tot[wave] = wtot;
