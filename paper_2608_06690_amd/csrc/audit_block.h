@@ -96,11 +96,12 @@ __device__ __forceinline__ void audit_4_requests(const AuditArgs& a, int r0, uns
   wviol += viol;
 }
 
-// Every thread of a workgroup of WAVES waves. Up to 16 requests are walked by a wave each, and more of them
-// where they are long on average (more than 4 tokens for up to 64 requests, 16 for up to 256, 64 for
-// more: lanes in fewer than 16 waves would have the longer ones in one line). Else a wave takes 64 requests at a time: those of up to 16 tokens (64 where it has many
-// of 17 to 64) are walked by one lane each, all at once, and longer ones by the whole wave, one after
-// the other. A token of a lane costs about 0.08 us, a request of a wave up to 0.8 us, both latency.
+// Every thread of a workgroup of WAVES waves. Up to 16 requests are walked by a wave each, and more
+// of them where they are long on average (more than 4 tokens for up to 64 requests, 16 for up to
+// 256, 64 for more: fewer than 16 waves with lanes at work would walk the longer ones in turn). Else
+// a wave takes 64 requests at a time: those of up to 16 tokens (64 where it has many of 17 to 64) are
+// walked by one lane each, all at once, and longer ones by the whole wave, one after the other. A
+// token of a lane costs about 0.08 us, a request of a wave up to 0.8 us, both latency.
 // (A rule on the mean length alone gave a long request among short ones to a lane: 200 requests of
 // one token and one of 500 took 46 us, now 4; a list of the long ones for all waves costs every
 // batch two block barriers, 10,000 requests of 1.6 tokens 14 us, now 9.)
