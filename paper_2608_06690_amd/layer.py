@@ -65,11 +65,9 @@ class AuditBuffers:
         return self
 
 
-_STEPS = ("route", "dispatch", "expert_ffn", "combine", "audit")
-_STEP_SET = frozenset(_STEPS)
-_steps_of = operator.attrgetter(*_STEPS)
-# the library calls that the steps make
-_calls_of = operator.attrgetter("pmpe_route", "pmpe_dispatch", "pmpe_expert_ffn", "pmpe_expert_ffn_train",
+# the steps of a forward and the library calls that they make, from the class's and the binding's names
+_steps_of = operator.itemgetter("route", "dispatch", "expert_ffn", "combine", "audit")
+_calls_of = operator.itemgetter("pmpe_route", "pmpe_dispatch", "pmpe_expert_ffn", "pmpe_expert_ffn_train",
                                 "pmpe_expert_ffn_fp8", "pmpe_combine", "pmpe_audit")
 
 
@@ -161,8 +159,10 @@ class PolicyMaskedMoE:
     def _plain_steps(self) -> bool:
         # the steps and their library calls are the ones written here: where a subclass, an object,
         # the class or the binding has one replaced, the calls are made one by one
-        return (type(self) is PolicyMaskedMoE and _STEP_SET.isdisjoint(self.__dict__)
-                and _steps_of(PolicyMaskedMoE) == _OWN_STEPS and _calls_of(N) == _OWN_CALLS)
+        d = self.__dict__
+        return (type(self) is PolicyMaskedMoE and "route" not in d and "dispatch" not in d and "expert_ffn" not in d
+                and "combine" not in d and "audit" not in d and _steps_of(PolicyMaskedMoE.__dict__) == _OWN_STEPS
+                and _calls_of(N.__dict__) == _OWN_CALLS)
 
     def _forward(self, x, words, b: LayerBuffers, audit: AuditBuffers, req_offset, stream, ffn: int,
                  fp8=None) -> None:
@@ -328,7 +328,7 @@ class PolicyMaskedMoE:
         return b
 
 
-_OWN_STEPS, _OWN_CALLS = _steps_of(PolicyMaskedMoE), _calls_of(N)
+_OWN_STEPS, _OWN_CALLS = _steps_of(PolicyMaskedMoE.__dict__), _calls_of(N.__dict__)
 
 
 class PrivateAdamW:
